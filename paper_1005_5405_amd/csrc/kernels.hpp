@@ -145,7 +145,7 @@ __device__ __forceinline__ const double* wall_consts(const Params& P, int wall, 
 // ------------------------------------------------------------------- S1 --
 // x-swept value (order 2) of node j at (ix, iy), read straight from global
 // memory; the same FP32 arithmetic as the stream kernel's x sweep.
-__device__ float xswept_value(const Params& P, const float* h, int ix, int iy,
+__device__ __forceinline__ float xswept_value(const Params& P, const float* h, int ix, int iy,
                               int j, int jx, int jy, int jz, double nwl, double nwr) {
   const double vx = P.vtab[jx];
   const float h0 = h[cell_off(P, ix, iy) + j];
@@ -169,7 +169,7 @@ __device__ float xswept_value(const Params& P, const float* h, int ix, int iy,
 // rest facing h = 0 gives n_w = 1 exactly), B = sum_out |v_n| w_j hhat_j;
 // n_w = (A + eps B) / D.  `order` selects the face value: 1 = adjacent cell,
 // 2 = Beam-Warming face value, from the x-swept state for y faces.
-__device__ double face_density(const Params& P, const float* h, int wall, int pos,
+__device__ __forceinline__ double face_density(const Params& P, const float* h, int wall, int pos,
                                int order, double nwl0, double nwl1, double nwr0, double nwr1,
                                double* red) {
   const int nx = P.nx, ny = P.ny, nv = P.nv, n1 = P.n[1], n2 = P.n[2];
@@ -280,8 +280,13 @@ __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, Wa
 // step, ..., U nodes per pass with every load of a pass issued before it
 // is used.  A y face of order 2 away from the corner columns reads the three
 // cells of each x sweep directly (no ghost value is needed there).
+// Inlined by force, like the functions above that take the problem by
+// reference: left to itself the compiler calls it in wall_batch_kernel with
+// a private copy of the 372-byte Params, and the two face launches of a batch
+// of ten cavities (16^3..24^3, 57^2..128^2 cells) take 247 + 296 us; inlined,
+// the problem's fields are scalar loads (batch step 10.01 -> 9.60 ms).
 template <int U>
-__device__ double face_b(const Params& P, const float* h, int wall, int pos, int order,
+__device__ __forceinline__ double face_b(const Params& P, const float* h, int wall, int pos, int order,
                          double nwl0, double nwl1, double nwr0, double nwr1, int j0, int step) {
   const int nx = P.nx, ny = P.ny, nv = P.nv, n1 = P.n[1], n2 = P.n[2];
   const int nax = (wall <= WALL_RIGHT) ? 0 : 1;
