@@ -23,28 +23,61 @@ namespace boltz {
 // dJ/dg (1 + eps h_a) to that of h_b, with
 // dJ/dg = k_a* lI_a* + k_b* lI_b* - k_a lI_a - k_b lI_b and the sample's own
 // coefficients k (FP32 table records or the FP64 values of the draw).
-// FIXED: the terms, divided by the cell's power-of-two scale S (inv_s =
-// 1/S), go to the 64-bit fixed-point accumulators acc (large ones to the
-// FP32 array ovf) as in the forward pass; else they are added in FP64 to ls
-// by compare-and-swap.
-template <bool FIXED>
-__device__ __forceinline__ void adj_add(double* ls, unsigned long long* acc, float* ovf, int j, double lg,
-                                        double inv_s, double f) {
-  if (FIXED) lds_add_hybrid(acc, ovf, j, lg * inv_s, f);
-  else lds_add_f64(&ls[j], lg * f);
-}
+// AdjFixed: the terms, divided by the cell's power-of-two scale S (inv_s =
+// 1/S), go to 64-bit fixed-point accumulators as in the forward pass; terms
+// of 2^18 S or more take the exact conversion (fixed_exact) up to 2^22 S,
+// and beyond that (or not finite) raise the flag: the cell's sums are then
+// formed again by AdjF64, FP64 compare-and-swap adds.
+struct AdjFixed {
+  unsigned long long* acc;
+  double inv_s;
+  unsigned* flag;
+  static constexpr double kWide = 4194304.0;  // 2^22: 512 such terms at one node stay within 64 bits
+  __device__ __forceinline__ void wide(int j, double k, double f) const {
+    const double x = k * f;
+    unsigned long long v;
+    if (fabs(x) < kWide && fixed_exact(x, v))
+      __hip_atomic_fetch_add(&acc[j], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+      *flag = 1u;
+  }
+  __device__ __forceinline__ void add(int a, int b, double lg, double fa, double fb) const {
+    // both values first; straight-line adds when the whole wavefront has
+    // them in the fixed-point window (a discarded sample adds 0)
+    const double ks = lg * inv_s;
+    const long long da = fixed_of(ks, fa), db = fixed_of(ks, fb);
+    const bool oa = in_fixed_window(da), ob = in_fixed_window(db);
+    if (__all(oa & ob)) {
+      __hip_atomic_fetch_add(&acc[a], (unsigned long long)da, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&acc[b], (unsigned long long)db, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      if (oa) __hip_atomic_fetch_add(&acc[a], (unsigned long long)da, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      else wide(a, ks, fa);
+      if (ob) __hip_atomic_fetch_add(&acc[b], (unsigned long long)db, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      else wide(b, ks, fb);
+    }
+  }
+};
 
-template <int BLOCK, bool TABLE, bool FIXED>
+struct AdjF64 {
+  double* ls;
+  __device__ __forceinline__ void add(int a, int b, double lg, double fa, double fb) const {
+    if (lg != 0.0) {
+      lds_add_f64(&ls[a], lg * fa);
+      lds_add_f64(&ls[b], lg * fb);
+    }
+  }
+};
+
+template <int BLOCK, bool TABLE, int PU, class Acc>
 __device__ __forceinline__ void gain_loss_adj(const Params& P, const TablesLDS& T, const float* hs,
-                                              const float* lI, double* ls, unsigned long long* acc, float* ovf,
-                                              double inv_s, uint32_t group, uint32_t step,
+                                              const float* lI, const Acc& A, uint32_t group, uint32_t step,
                                               const uint2* __restrict__ tidx,
                                               const float4* __restrict__ tcoef) {
   const int tid = threadIdx.x;
   const double eps = P.eps;
   const uint32_t nt = (uint32_t)P.n_pairs;
   if (TABLE) {
-    constexpr int PU = 4;
     const uint2* ri = tidx + (int64_t)group * nt;
     const float4* rk = tcoef + (int64_t)group * nt;
     // one pass: PU records per thread; in the masked (last) pass slots past
@@ -60,30 +93,25 @@ __device__ __forceinline__ void gain_loss_adj(const Params& P, const TablesLDS& 
         id[u] = ok[u] ? ri[m] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[m] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
+      // the six gathers of every record in flight together
+      float l[PU][4], ha[PU], hb[PU];
+#pragma unroll
+      for (int u = 0; u < PU; ++u) {
+        const int a = (int)(id[u].x & 0xFFFFu), b = (int)(id[u].x >> 16);
+        l[u][0] = lI[id[u].y & 0xFFFFu];
+        l[u][1] = lI[id[u].y >> 16];
+        l[u][2] = lI[a];
+        l[u][3] = lI[b];
+        ha[u] = hs[a];
+        hb[u] = hs[b];
+      }
 #pragma unroll
       for (int u = 0; u < PU; ++u) {
         if (!ok[u]) continue;
-        const int a = (int)(id[u].x & 0xFFFFu), b = (int)(id[u].x >> 16);
-        const int as = (int)(id[u].y & 0xFFFFu), bs = (int)(id[u].y >> 16);
-        const double lg = fma((double)kk[u].x, (double)lI[as], (double)kk[u].y * (double)lI[bs]) -
-                          fma((double)kk[u].z, (double)lI[a], (double)kk[u].w * (double)lI[b]);
-        const double ha = (double)hs[a], hb = (double)hs[b];
-        if (FIXED) {
-          // both values first; straight-line adds when the whole wavefront
-          // has them in the fixed-point window (a discarded sample adds 0)
-          const double ks = lg * inv_s, fa = fma(eps, hb, 1.0), fb = fma(eps, ha, 1.0);
-          const long long da = fixed_of(ks, fa), db = fixed_of(ks, fb);
-          if (__all(in_fixed_window(da) & in_fixed_window(db))) {
-            __hip_atomic_fetch_add(&acc[a], (unsigned long long)da, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            __hip_atomic_fetch_add(&acc[b], (unsigned long long)db, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          } else {
-            lds_add_fixed_or(acc, ovf, a, da, ks, fa);
-            lds_add_fixed_or(acc, ovf, b, db, ks, fb);
-          }
-        } else if (lg != 0.0) {
-          adj_add<FIXED>(ls, acc, ovf, a, lg, inv_s, fma(eps, hb, 1.0));
-          adj_add<FIXED>(ls, acc, ovf, b, lg, inv_s, fma(eps, ha, 1.0));
-        }
+        const double lg = fma((double)kk[u].x, (double)l[u][0], (double)kk[u].y * (double)l[u][1]) -
+                          fma((double)kk[u].z, (double)l[u][2], (double)kk[u].w * (double)l[u][3]);
+        A.add((int)(id[u].x & 0xFFFFu), (int)(id[u].x >> 16), lg, fma(eps, (double)hb[u], 1.0),
+              fma(eps, (double)ha[u], 1.0));
       }
     };
     uint32_t m0 = tid;
@@ -96,57 +124,158 @@ __device__ __forceinline__ void gain_loss_adj(const Params& P, const TablesLDS& 
         const double lg = fma(p.kas, (double)lI[p.as], p.kbs * (double)lI[p.bs]) -
                           fma(p.ka, (double)lI[p.a], p.kb * (double)lI[p.b]);
         const double ha = (double)hs[p.a], hb = (double)hs[p.b];
-        adj_add<FIXED>(ls, acc, ovf, p.a, lg, inv_s, fma(eps, hb, 1.0));
-        adj_add<FIXED>(ls, acc, ovf, p.b, lg, inv_s, fma(eps, ha, 1.0));
+        A.add(p.a, p.b, lg, fma(eps, hb, 1.0), fma(eps, ha, 1.0));
       }
     }
   }
 }
 
 // Dynamic LDS of the collide adjoint: the collide kernel's fixed-point layout
-// (h^s tile, FP32 array, 64-bit accumulators), with FIXED a second FP32
-// array (large terms of the adjoint sums), then the tables and the per-axis
-// table of y . psi.
-__host__ __device__ inline size_t collide_adj_lds(int nv, int ns, bool sampler, bool fixed) {
-  return CollideLDS::tile(nv) + CollideLDS::acc(nv, ACC_FIXED) + (fixed ? CollideLDS::tile(nv) : 0) +
-         TablesLDS::bytes(ns, sampler) + 8 * (size_t)ns;
+// (h^s tile, FP32 array, 64-bit accumulators), then the tables and the
+// per-axis table of y . psi.  The block sums (25 doubles per wavefront) use
+// the accumulators' region between the two pair passes.
+__host__ __device__ inline size_t collide_adj_acc(int nv, int block) {
+  const size_t a = ((size_t)nv * 8 + 15) & ~(size_t)15, r = (size_t)25 * (block / 64) * 8;
+  return a > r ? a : ((r + 15) & ~(size_t)15);
+}
+__host__ __device__ inline size_t collide_adj_lds(int nv, int ns, bool sampler, int block) {
+  return 2 * CollideLDS::tile(nv) + collide_adj_acc(nv, block) + TablesLDS::bytes(ns, sampler) + 8 * (size_t)ns;
 }
 
-// static LDS of the collide adjoint (reduction scratch)
-__host__ __device__ inline size_t collide_adj_static_lds(int block) {
-  return (20 * (size_t)(block / 64) + 20) * sizeof(double);
+// static LDS of the collide adjoint (maxima per wavefront, flag)
+__host__ __device__ inline size_t collide_adj_static_lds(int block) { return 8 * (size_t)(block / 64) + 16; }
+
+// Sum of 5 values per lane over the wavefront: lane 32 b5 + 16 b4 + 8 b3
+// holds value k = 3 b5 + 2 b4 + b3 (valid where 2 b4 + b3 < 3 - b5).
+__device__ __forceinline__ double wave_fold5(double (&v)[5], int lane) {
+  fold_half<5, 32, 0>(v, lane);
+  fold_half<3, 16, 0>(v, lane);
+  fold_half<2, 8, kDppMirror>(v, lane);
+  double t = v[0];
+  t += dpp_f64<kDppHalfMirror>(t);
+  t += dpp_f64<kDppXor2>(t);
+  t += dpp_f64<kDppXor1>(t);
+  return t;
+}
+
+// Largest value over the wavefront, in every lane (no LDS traffic).
+__device__ __forceinline__ double wave_max(double v) {
+  v = fmax(v, dpp_f64<kDppXor1>(v));
+  v = fmax(v, dpp_f64<kDppXor2>(v));
+  v = fmax(v, dpp_f64<kDppHalfMirror>(v));
+  v = fmax(v, dpp_f64<kDppMirror>(v));
+  const unsigned a = (unsigned)__double2loint(v), b = (unsigned)__double2hiint(v);
+  const auto l = __builtin_amdgcn_permlane16_swap(a, a, false, false), h = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  v = fmax(__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1]));
+  const unsigned c = (unsigned)__double2loint(v), d = (unsigned)__double2hiint(v);
+  const auto m = __builtin_amdgcn_permlane32_swap(c, c, false, false), n = __builtin_amdgcn_permlane32_swap(d, d, false, false);
+  return fmax(__hiloint2double((int)n[0], (int)m[0]), __hiloint2double((int)n[1], (int)m[1]));
+}
+
+// V consecutive values at p, which V = 4 finds on a 16-byte boundary (one or
+// two 16-byte accesses, no bank conflicts between neighbouring lanes).
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+template <int V>
+__device__ __forceinline__ void get_v(const float* p, float (&v)[V]) {
+  if constexpr (V == 4) {
+    const f32x4 t = *reinterpret_cast<const f32x4*>(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
+  } else {
+    v[0] = p[0];
+  }
+}
+template <int V>
+__device__ __forceinline__ void put_v(float* p, const float (&v)[V]) {
+  if constexpr (V == 4) *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+  else p[0] = v[0];
+}
+template <int V>
+__device__ __forceinline__ void get_v(const unsigned long long* p, unsigned long long (&v)[V]) {
+  if constexpr (V == 4) {
+    const u64x2* q = reinterpret_cast<const u64x2*>(p);
+    const u64x2 a = q[0], b = q[1];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+  } else {
+    v[0] = p[0];
+  }
+}
+template <int V>
+__device__ __forceinline__ void clear_v(unsigned long long* p) {
+  if constexpr (V == 4) {
+    u64x2* q = reinterpret_cast<u64x2*>(p);
+    q[0] = u64x2{0ull, 0ull};
+    q[1] = u64x2{0ull, 0ull};
+  } else {
+    p[0] = 0ull;
+  }
+}
+// adjoint values in global memory (read once, written once)
+template <int V>
+__device__ __forceinline__ void load_lam(const double* p, double (&v)[V]) {
+  if constexpr (V == 4) {
+    const f64x2* q = reinterpret_cast<const f64x2*>(p);
+    const f64x2 a = q[0], b = q[1];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+  } else {
+    v[0] = p[0];
+  }
+}
+template <int V>
+__device__ __forceinline__ void store_lam(double* p, const double (&v)[V]) {
+  if constexpr (V == 4) {
+    f64x2* q = reinterpret_cast<f64x2*>(p);
+    __builtin_nontemporal_store(f64x2{v[0], v[1]}, &q[0]);
+    __builtin_nontemporal_store(f64x2{v[2], v[3]}, &q[1]);
+  } else {
+    p[0] = v[0];
+  }
 }
 
 // Reverse mode of collide_kernel: lo = adjoint of h^{n+1}, ls = adjoint of
-// h^s (FP64; ls may equal lo, each cell is read before it is written).  Per
-// cell the forward pass is recomputed in LDS (h^c and the correction's x);
-// then with z_k = sum_j lo_j F^c_j psi_k / eps and M y = z,
+// h^s (FP64; ls may equal lo, each node is read before it is written, by the
+// thread that writes it).  Per cell the forward pass is recomputed in LDS
+// (h^c and the correction's x); then with z_k = sum_j lo_j F^c_j psi_k / eps
+// and M y = z,
 //   lhc_j = lo_j (1 + x.psi_j) - eps w_j (y.psi_j)(x.psi_j)   (adjoint of h^c)
 //   lI_j  = lhc_j - eps w_j (y.psi_j)      (adjoint of the increment of h)
 // and ls = lhc plus the sample terms of gain_loss_adj.  Without the
 // correction, or when M is not positive definite (status bit 1, as in the
 // forward pass), x = y = 0.  LDS reuse: h^c is overwritten by lI (FP32), the
-// forward's fixed-point accumulators by the adjoint sums: FIXED, 64-bit fixed
-// point in units of S 2^-32 with S the power of two above the cell's
-// max |lhc| (terms of 2^18 S or more in a second FP32 array); else FP64.
-template <int BLOCK, bool TABLE, bool FIXED>
-__global__ __launch_bounds__(BLOCK) void collide_adj_kernel(Params P, const float* __restrict__ hs_g,
+// forward's accumulators by the adjoint sums, 64-bit fixed point in units of
+// S 2^-32 with S the power of two above the cell's max |lhc|.
+//
+// V consecutive nodes of one velocity row per thread and group (V = 4 where
+// nv_z is a multiple of 4, else 1).  lo is read once, into 8 registers a
+// thread while the forward pair loop runs, and becomes lhc there; the next
+// cell's lo and h^s are requested in the last pass.  Bound by the LDS (two
+// gathers and four adds, then six gathers and two adds per pair), then by
+// the node passes' latency: one workgroup per CU on 20^3, so 1024 threads.
+// 64x64 cavity, 20^3, 20 000 shared pairs, us per cell: 45.7 with 512
+// threads, three reads of lo and per-node LDS accesses; now 37 (21.8 of them
+// the two pair loops, 2.0 h^c, 1.3 + 1.6 sums and fold, 2.0 solves, 4.0
+// adjoints, 4.5 output, staging and barrier).
+constexpr int kAdjKeep = 8;  // lo values per thread kept in registers
+
+template <int BLOCK, bool TABLE, int V>
+__global__ __launch_bounds__(BLOCK, 4) void collide_adj_kernel(Params P, const float* __restrict__ hs_g,
                                                             const double* lo_g, double* ls_g, uint32_t step,
                                                             uint32_t flags, const uint2* __restrict__ tidx,
                                                             const float4* __restrict__ tcoef) {
   extern __shared__ __align__(16) unsigned char dsm[];
-  __shared__ double red[20 * (BLOCK / 64)];
-  __shared__ double tot[20];
+  __shared__ double mred[BLOCK / 64];
+  __shared__ unsigned wide_flag;
+  constexpr int NG = kAdjKeep / V;        // groups of V nodes kept per thread
+  constexpr int NW = BLOCK / 64;
   const int nv = P.nv, n0 = P.n[0], n1 = P.n[1], n2 = P.n[2], ns = n0 + n1 + n2;
+  const int ng = nv / V;                  // groups of the cell
   const int64_t ncells = (int64_t)P.nx * P.ny;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   float* hs = reinterpret_cast<float*>(dsm);
   float* accf = reinterpret_cast<float*>(dsm + CollideLDS::tile(nv));
   unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(dsm + 2 * CollideLDS::tile(nv));
   double* lsh = reinterpret_cast<double*>(acc64);
-  unsigned char* after = dsm + CollideLDS::tile(nv) + CollideLDS::acc(nv, ACC_FIXED);
-  float* ovf = FIXED ? reinterpret_cast<float*>(after) : nullptr;
-  unsigned char* tb = after + (FIXED ? CollideLDS::tile(nv) : 0);
+  double* red = lsh;                      // block sums, between the pair passes
+  unsigned char* tb = dsm + 2 * CollideLDS::tile(nv) + collide_adj_acc(nv, BLOCK);
   TablesLDS T;
   load_tables(P, tb, !TABLE, T);
   double* yt = reinterpret_cast<double*>(tb + TablesLDS::bytes(ns, !TABLE));
@@ -158,144 +287,245 @@ __global__ __launch_bounds__(BLOCK) void collide_adj_kernel(Params P, const floa
   const double* omz = T.om + n0 + n1;
   const bool correct = !(flags & 1u);
   const double eps = P.eps;
-  // adjoint of h^c at node j = (jx, jy, jz)
-  auto lam_hc = [&](double l, int jx, int jy, int jz, double& lI) -> double {
-    if (!correct) {
-      lI = l;
-      return l;
-    }
-    const double xpsi = (T.xt[jx] + T.xt[n0 + jy]) + T.xt[n0 + n1 + jz];
-    const double ypsi = (yt[jx] + yt[n0 + jy]) + yt[n0 + n1 + jz];
-    const double ewy = eps * ((omx[jx] * omy[jy]) * omz[jz]) * ypsi;
-    const double lhc = fma(l, xpsi, l) - ewy * xpsi;
-    lI = lhc - ewy;
-    return lhc;
+  // this thread's index, hidden from the optimiser: the passes below form
+  // their node indices from it, which otherwise stay in registers (hoisted out
+  // of the cell loop) across the pair loops and spill
+  auto here = [&]() {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    return t;
   };
-  for (int64_t cell = blockIdx.x; cell < ncells; cell += gridDim.x) {
-    const float* src = hs_g + cell * nv;
-    const double* lo = lo_g + cell * nv;
-    if ((nv & 3) == 0 && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-      const float4* s4 = reinterpret_cast<const float4*>(src);
-      float4* d4 = reinterpret_cast<float4*>(hs);
-#pragma unroll 4
-      for (int j = tid; j < (nv >> 2); j += BLOCK) d4[j] = s4[j];
+  // lo of this thread's groups; groups past the registers (i >= NG * BLOCK)
+  // read theirs again in each pass
+  double lam[NG][V];
+  auto load_lo = [&](const double* lo) {
+    const int t = here();
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      load_lam<V>(lo + min(t + g * BLOCK, ng - 1) * V, lam[g]);
+    }
+  };
+  // h^s of the next cell waits in registers during the second pair loop
+  constexpr int NR = prefetch_regs<BLOCK>();
+  const int nv4 = nv >> 2;
+  const bool pvec = V == 4 && nv4 <= NR * BLOCK && (reinterpret_cast<uintptr_t>(hs_g) & 15) == 0;
+  Prefetch<NR> pre;
+  auto stage = [&](const float* src) {
+    if (pvec) {
+      pre.store(hs, tid, BLOCK, nv4);
     } else {
       for (int j = tid; j < nv; j += BLOCK) hs[j] = src[j];
     }
-    {
-      uint4* z = reinterpret_cast<uint4*>(accf);
-      const int nz = (int)(CollideLDS::acc(nv, ACC_FIXED) / 16);
-      for (int i = tid; i < nz; i += BLOCK) z[i] = make_uint4(0u, 0u, 0u, 0u);
+  };
+  // velocity row (jx, jy) and first z node of group i
+  auto decode = [&](int i, int& jx, int& jy, int& jz) {
+    const int row = div_small(i * V, n2);
+    jz = i * V - row * n2;
+    jx = div_small(row, n1);
+    jy = row - jx * n1;
+  };
+  // adjoints of h^c (returned) and of the increment of the nodes of group i
+  auto lam_group = [&](int i, const double (&l)[V], double (&lhc)[V], double (&lI)[V]) {
+    if (!correct) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) lhc[e] = lI[e] = l[e];
+      return;
     }
+    int jx, jy, jz;
+    decode(i, jx, jy, jz);
+    const double xa = T.xt[jx] + T.xt[n0 + jy], ya = yt[jx] + yt[n0 + jy], wa = omx[jx] * omy[jy];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const double xpsi = xa + T.xt[n0 + n1 + jz + e], ypsi = ya + yt[n0 + n1 + jz + e];
+      const double ewy = eps * (wa * omz[jz + e]) * ypsi;
+      lhc[e] = fma(l[e], xpsi, l[e]) - ewy * xpsi;
+      lI[e] = lhc[e] - ewy;
+    }
+  };
+  int64_t cell = blockIdx.x;
+  if (cell < ncells) {
+    if (pvec) pre.load(hs_g + cell * nv, tid, BLOCK, nv4);
+    stage(hs_g + cell * nv);
+  }
+  for (int j = tid; j < nv; j += BLOCK) accf[j] = 0.0f;
+  for (int j = tid; j < nv; j += BLOCK) acc64[j] = 0ull;
+  for (; cell < ncells; cell += gridDim.x) {
+    const double* lo = lo_g + cell * nv;
+    load_lo(lo);
     __syncthreads();
-    // ---- forward: increments and h^c
+    // ---- forward: increments and h^c, and the sums z
     const uint32_t group = (P.sample_group == 0) ? 0u : (uint32_t)(cell / P.sample_group);
     gain_loss<BLOCK, TABLE, ACC_FIXED>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
     __syncthreads();
-    for (int j = tid; j < nv; j += BLOCK) {
-      const double dh = (double)accf[j] + from_fixed(acc64[j]);
-      accf[j] = (float)((double)hs[j] + dh);
+    double zs[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    auto hc_group = [&](int i, const double (&l)[V]) {
+      int jx, jy, jz;
+      decode(i, jx, jy, jz);
+      const double a = vx[jx], b = vy[jy];
+      double us = 0.0, uz = 0.0, uzz = 0.0;
+      float f[V], h[V];
+      unsigned long long q[V];
+      get_v<V>(accf + i * V, f);
+      get_v<V>(hs + i * V, h);
+      get_v<V>(acc64 + i * V, q);
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const double dh = (double)f[e] + from_fixed(q[e]);
+        f[e] = (float)((double)h[e] + dh);
+        const double u = l[e] * fma(eps, (double)f[e], 1.0), c = vz[jz + e];
+        us += u;
+        uz += c * u;
+        uzz += (c * c) * u;
+      }
+      put_v<V>(accf + i * V, f);
+      zs[0] += us;
+      zs[1] += a * us;
+      zs[2] += b * us;
+      zs[3] += uz;
+      zs[4] += (a * a + b * b) * us + uzz;
+    };
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int i = here() + g * BLOCK;
+      if (i < ng) hc_group(i, lam[g]);
+    }
+    for (int i = tid + NG * BLOCK; i < ng; i += BLOCK) {
+      double l[V];
+      load_lam<V>(lo + i * V, l);
+      hc_group(i, l);
     }
     if (correct) {
       __syncthreads();
       double acc[20];
       correction_sums<BLOCK>(T, P.zmom, hs, accf, n0, n1, n2, acc);
-      block_sum20_lds<BLOCK>(acc, red, tot);
-      double zs[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-      NodeWalk walk(tid, BLOCK, n1, n2);
-      // (unrolled: the global loads of lo of several nodes in flight together)
-#pragma unroll 4
-      for (int j = tid; j < nv; j += BLOCK, walk.next()) {
-        const double u = lo[j] * fma(eps, (double)accf[j], 1.0);
-        const double a = vx[walk.jx], b = vy[walk.jy], c = vz[walk.jz];
-        zs[0] += u;
-        zs[1] += a * u;
-        zs[2] += b * u;
-        zs[3] += c * u;
-        zs[4] += ((a * a + b * b) + c * c) * u;
-      }
-      block_sum<5, BLOCK>(zs, red);
-      if (tid < 64) {
-        // wavefront 0: M x = r and M y = z, then x . psi and y . psi per axis
-        double M[15], r[5], z[5], x[5], y[5];
-#pragma unroll
-        for (int k = 0; k < 15; ++k) M[k] = T.m0[k] + eps * tot[k];
-#pragma unroll
-        for (int k = 0; k < 5; ++k) {
-          r[k] = -eps * tot[15 + k];
-          z[k] = zs[k] * P.inv_eps;
+      const int rows = n0 * n1, nwd = rows >= BLOCK ? NW : (rows + 63) / 64;
+      {
+        const double z = wave_fold5(zs, lane);
+        const int b5 = (lane >> 5) & 1, pos = 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
+        if ((lane & 7) == 0 && pos < 3 - b5) red[(20 + 3 * b5 + pos) * NW + wid] = z;
+        if (wid < nwd) {
+          const double s = wave_fold20(acc, lane);
+          const int b4 = (lane >> 4) & 1, b3 = (lane >> 3) & 1, b2 = (lane >> 2) & 1, b1 = (lane >> 1) & 1;
+          const int p = 3 * b3 + 2 * b2 + b1;
+          if (((lane & 1) == 0) && (b3 ? (b2 == 0) : (p < 3))) red[(10 * b5 + 5 * b4 + p) * NW + wid] = s;
         }
-        const bool ok = solve5(M, r, x);
-        solve5(M, z, y);
-        if (!ok) {
+      }
+      __syncthreads();
+      // lo again (from cache), for the passes after the solve: kept across
+      // the sums and the solve it would spill
+      load_lo(lo);
+      if (wid < 2) {
+        // wavefront 0: M x = r, wavefront 1: M y = z; then x . psi, y . psi
+        // per axis
+        double t = 0.0;
+        if (lane < 25)
+          for (int w = 0; w < (lane < 20 ? nwd : NW); ++w) t += red[lane * NW + w];
+        const const_f64* m0c = (const const_f64*)P.m0;
+        const int rhs = __builtin_amdgcn_readfirstlane(wid);
+        double M[15], r[5], x[5];
 #pragma unroll
-          for (int k = 0; k < 5; ++k) x[k] = y[k] = 0.0;
+        for (int k = 0; k < 15; ++k) M[k] = m0c[k] + eps * lane_value(t, k);
+#pragma unroll
+        for (int k = 0; k < 5; ++k) r[k] = (rhs ? P.inv_eps : -eps) * lane_value(t, (rhs ? 20 : 15) + k);
+        if (!solve5(M, r, x)) {
+#pragma unroll
+          for (int k = 0; k < 5; ++k) x[k] = 0.0;
           if (tid == 0) atomicOr(P.status, 1u);
         }
-        for (int i = tid; i < ns; i += 64) {
+        double* tab = rhs ? yt : T.xt;
+        for (int i = lane; i < ns; i += 64) {
           const double v = T.v[i], v2 = v * v;
-          T.xt[i] = i < n0 ? x[1] * v + x[4] * v2 : (i < n0 + n1 ? x[2] * v + x[4] * v2 : x[0] + x[3] * v + x[4] * v2);
-          yt[i] = i < n0 ? y[1] * v + y[4] * v2 : (i < n0 + n1 ? y[2] * v + y[4] * v2 : y[0] + y[3] * v + y[4] * v2);
+          tab[i] = i < n0 ? x[1] * v + x[4] * v2 : (i < n0 + n1 ? x[2] * v + x[4] * v2 : x[0] + x[3] * v + x[4] * v2);
         }
       }
       __syncthreads();
     }
-    // ---- adjoints of h^c and of the increment (each thread its own nodes)
+    // ---- adjoints of h^c (lam becomes lhc) and of the increment
     double scale = 1.0, inv_scale = 1.0;
     {
       double mx = 0.0;
-      NodeWalk walk(tid, BLOCK, n1, n2);
-#pragma unroll 4
-      for (int j = tid; j < nv; j += BLOCK, walk.next()) {
-        double lI;
-        const double lhc = lam_hc(lo[j], walk.jx, walk.jy, walk.jz, lI);
-        accf[j] = (float)lI;
-        if (FIXED) {
-          acc64[j] = 0ull;
-          ovf[j] = 0.0f;
-          mx = fmax(mx, fabs(lhc));
-        } else {
-          lsh[j] = lhc;
-        }
-      }
-      if (FIXED) {
-        // S = 2^e > max |lhc| of the cell (1 for an all-zero or non-finite cell)
+      auto lI_group = [&](int i, double (&l)[V]) {
+        double lhc[V], lI[V];
+        lam_group(i, l, lhc, lI);
+        float f[V];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-        if ((tid & 63) == 0) red[tid >> 6] = mx;
+        for (int e = 0; e < V; ++e) {
+          f[e] = (float)lI[e];
+          mx = fmax(mx, fabs(lhc[e]));
+          l[e] = lhc[e];
+        }
+        put_v<V>(accf + i * V, f);
+        clear_v<V>(acc64 + i * V);
+      };
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const int i = here() + g * BLOCK;
+        if (i < ng) lI_group(i, lam[g]);
       }
+      for (int i = tid + NG * BLOCK; i < ng; i += BLOCK) {
+        double l[V];
+        load_lam<V>(lo + i * V, l);
+        lI_group(i, l);
+      }
+      // S = 2^e > max |lhc| of the cell (1 for an all-zero or non-finite cell)
+      mx = wave_max(mx);
+      if (lane == 0) mred[wid] = mx;
+      if (tid == 0) wide_flag = 0u;
     }
     __syncthreads();
-    if (FIXED) {
-      double mx = 0.0;
-      for (int w = 0; w < BLOCK / 64; ++w) mx = fmax(mx, red[w]);
+    {
+      const double mx = lane_value(wave_max(lane < NW ? mred[lane] : 0.0), 0);
       if (mx > 0.0 && isfinite(mx)) {
-        const int e = ilogb(mx) + 1;
+        const int e = __builtin_amdgcn_frexp_exp(mx);  // mx = f 2^e, 1/2 <= f < 1
         scale = ldexp(1.0, e);
         inv_scale = ldexp(1.0, -e);
       }
     }
-    gain_loss_adj<BLOCK, TABLE, FIXED>(P, T, hs, accf, lsh, acc64, ovf, inv_scale, group, step, tidx, tcoef);
+    const int64_t next = cell + gridDim.x;
+    if (pvec && next < ncells) pre.load(hs_g + next * nv, tid, BLOCK, nv4);
+    gain_loss_adj<BLOCK, TABLE, 4>(P, T, hs, accf, AdjFixed{acc64, inv_scale, &wide_flag}, group, step, tidx, tcoef);
     __syncthreads();
+    const bool wide = wide_flag != 0u;
+    if (wide) {
+      // (rare) a term beyond the fixed-point range: the sums in FP64
+      __syncthreads();
+      for (int j = tid; j < nv; j += BLOCK) lsh[j] = 0.0;
+      __syncthreads();
+      gain_loss_adj<BLOCK, TABLE, 1>(P, T, hs, accf, AdjF64{lsh}, group, step, tidx, tcoef);
+      __syncthreads();
+    }
+    // ---- ls = lhc + the sums; the accumulators are left cleared and the
+    // next cell's lo and h^s requested
     bool finite = true;
     double* dst = ls_g + cell * nv;
-    {
-      NodeWalk walk(tid, BLOCK, n1, n2);
-#pragma unroll 4
-      for (int j = tid; j < nv; j += BLOCK, walk.next()) {
-        double v;
-        if (FIXED) {
-          double lI;
-          v = lam_hc(lo[j], walk.jx, walk.jy, walk.jz, lI) + scale * (from_fixed(acc64[j]) + (double)ovf[j]);
-        } else {
-          v = lsh[j];
-        }
-        finite = finite && isfinite(v);
-        dst[j] = v;
+    auto out_group = [&](int i, const double (&lhc)[V]) {
+      unsigned long long q[V];
+      get_v<V>(acc64 + i * V, q);
+      clear_v<V>(acc64 + i * V);
+      float z[V];
+      double v[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        v[e] = lhc[e] + (wide ? __longlong_as_double((long long)q[e]) : scale * from_fixed(q[e]));
+        z[e] = 0.0f;
+        finite = finite && isfinite(v[e]);
       }
+      put_v<V>(accf + i * V, z);
+      store_lam<V>(dst + i * V, v);
+    };
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int i = here() + g * BLOCK;
+      if (i < ng) out_group(i, lam[g]);
     }
+    for (int i = tid + NG * BLOCK; i < ng; i += BLOCK) {
+      double l[V], lhc[V], lI[V];
+      load_lam<V>(lo + i * V, l);
+      lam_group(i, l, lhc, lI);
+      out_group(i, lhc);
+    }
+    if (next < ncells) stage(hs_g + next * nv);
     if (!finite) atomicOr(P.status, 2u);
-    __syncthreads();
   }
 }
 

@@ -61,8 +61,7 @@ struct boltz_ctx {
   // adjoint: collide-adjoint launch (block, dynamic LDS, grid) of the two
   // variants, and the scratch of BOLTZ_WITH_ADJOINT
   bool adj_supported = false;
-  int adj_block = 256;
-  bool adj_fixed[2] = {false, false};
+  int adj_block[2] = {256, 256};
   size_t adj_lds[2] = {0, 0};
   int64_t adj_grid[2] = {0, 0};
   float* adj_hs = nullptr;      // post-stream state recomputed by boltz_step_adjoint
@@ -217,29 +216,34 @@ bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
   return true;
 }
 
-// Block size of the collide adjoint (at least the FP64-sum layout, the
-// forward's fixed-point layout plus a y . psi table, must fit in LDS): 256
-// threads when four workgroups fit per CU, else 512.  fixed[t]: the
-// fixed-point adjoint sums (one more FP32 array) fit as well, for the
-// drawn-pair [0] and shared-table [1] variants.  false when nothing fits.
-bool pick_adjoint(int nv, int ns, int& block, bool (&fixed)[2]) {
-  const size_t dyn = collide_adj_lds(nv, ns, true, false);
-  if (dyn + collide_adj_static_lds(512) > kLdsBytes) return false;
-  block = (4 * (dyn + collide_adj_static_lds(256)) <= kLdsBytes) ? 256 : 512;
-  for (int t = 0; t < 2; ++t)
-    fixed[t] = collide_adj_lds(nv, ns, t == 0, true) + collide_adj_static_lds(block) <= kLdsBytes;
-  return true;
+// Collide adjoint: false when its layout (with the sampler's tables) does
+// not fit next to 3360 bytes of reduction scratch.
+bool adjoint_fits(int nv, int ns) { return collide_adj_lds(nv, ns, true, 64) + 1440 <= kLdsBytes; }
+
+// Threads per workgroup of the collide adjoint: its 128 registers a thread
+// allow 1024 threads per CU, so one workgroup of 1024 where the LDS or the
+// number of cells leaves a CU one cell, two of 512, else four of 256 (64x64
+// cavity, 20^3, shared pairs, one cell per CU by its LDS: 1024 threads 0.59
+// ms, 512 threads of the earlier form 0.71 ms).
+int adjoint_block(int nv, int ns, bool sampler, int64_t ncells, int ncu) {
+  const int64_t cells = (ncells + ncu - 1) / ncu;
+  auto fit = [&](int block) {
+    return (int64_t)(kLdsBytes / (collide_adj_lds(nv, ns, sampler, block) + collide_adj_static_lds(block)));
+  };
+  if (cells >= 4 && fit(256) >= 4) return 256;
+  if (cells >= 2 && fit(512) >= 2) return 512;
+  return 1024;
 }
 
-const void* collide_adj_fn(int block, bool table, bool fixed) {
-#define BOLTZ_ADJ_FN(B)                                                                                   \
-  if (block == B)                                                                                         \
-    return table ? (fixed ? (const void*)collide_adj_kernel<B, true, true> : (const void*)collide_adj_kernel<B, true, false>) \
-                 : (fixed ? (const void*)collide_adj_kernel<B, false, true> : (const void*)collide_adj_kernel<B, false, false>);
-  BOLTZ_ADJ_FN(256)
-  BOLTZ_ADJ_FN(512)
-#undef BOLTZ_ADJ_FN
-  return nullptr;
+template <int B>
+const void* collide_adj_fn_b(bool table, bool vec) {
+  return table ? (vec ? (const void*)collide_adj_kernel<B, true, 4> : (const void*)collide_adj_kernel<B, true, 1>)
+               : (vec ? (const void*)collide_adj_kernel<B, false, 4> : (const void*)collide_adj_kernel<B, false, 1>);
+}
+
+const void* collide_adj_fn(int block, bool table, bool vec) {
+  return block == 256 ? collide_adj_fn_b<256>(table, vec)
+                      : (block == 512 ? collide_adj_fn_b<512>(table, vec) : collide_adj_fn_b<1024>(table, vec));
 }
 
 // table: shared records; else pairs drawn in the kernel by the node law or,
@@ -772,26 +776,20 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
     if (ea == hipSuccess && per_cu < 1) ea = hipErrorInvalidConfiguration;
     c->collide_per_cu[0] = c->collide_per_cu[1] = per_cu;
   }
-  c->adj_supported = ea == hipSuccess && !seq && pick_adjoint(c->nv, nsum, c->adj_block, c->adj_fixed);
+  c->adj_supported = ea == hipSuccess && !seq && adjoint_fits(c->nv, nsum);
   for (int t = 0; t < 2 && ea == hipSuccess && c->adj_supported; ++t) {
-    // the fixed-point layout when the runtime accepts its LDS size, else FP64 sums
-    for (int attempt = 0; attempt < 2; ++attempt) {
-      const void* fn = collide_adj_fn(c->adj_block, t == 1, c->adj_fixed[t]);
-      c->adj_lds[t] = collide_adj_lds(c->nv, nsum, t == 0, c->adj_fixed[t]);
-      ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->adj_lds[t]);
-      int per_cu = 0;
-      if (ea == hipSuccess)
-        ea = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, c->adj_block, c->adj_lds[t]);
-      if (ea == hipSuccess && per_cu < 1) ea = hipErrorInvalidConfiguration;
-      if (ea == hipSuccess) {
-        const int64_t cap = (int64_t)per_cu * (ncu < 1 ? 1 : ncu);
-        c->adj_grid[t] = c->ncells < cap ? c->ncells : cap;
-        break;
-      }
-      if (!c->adj_fixed[t]) break;
-      (void)hipGetLastError();
-      c->adj_fixed[t] = false;
-    }
+    const int block = adjoint_block(c->nv, nsum, t == 0, c->ncells, ncu < 1 ? 1 : ncu);
+    const void* fn = collide_adj_fn(block, t == 1, c->n[2] % 4 == 0);
+    c->adj_block[t] = block;
+    c->adj_lds[t] = collide_adj_lds(c->nv, nsum, t == 0, block);
+    // (per kernel, shared by every context: the largest size)
+    ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)(kLdsBytes - collide_adj_static_lds(block)));
+    int per_cu = 0;
+    if (ea == hipSuccess) ea = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, c->adj_lds[t]);
+    if (ea == hipSuccess && per_cu < 1) ea = hipErrorInvalidConfiguration;
+    const int64_t cap = (int64_t)per_cu * (ncu < 1 ? 1 : ncu);
+    c->adj_grid[t] = c->ncells < cap ? c->ncells : cap;
   }
   if (ea != hipSuccess) {
     boltz_destroy(c);
@@ -1196,24 +1194,20 @@ static int launch_stream_adj(boltz_ctx* c, const WallArgs& W, const double* lo, 
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "stream adjoint launch");
 }
 
-extern "C++" template <int B, bool TABLE, bool FIXED>
-static void launch_collide_adj_v(boltz_ctx* c, const float* hs, const double* lo, double* ls, uint32_t s32,
-                                 uint32_t flags, hipStream_t st) {
-  const int t = TABLE ? 1 : 0;
-  hipLaunchKernelGGL((collide_adj_kernel<B, TABLE, FIXED>), dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t],
-                     st, c->P, hs, lo, ls, s32, flags, c->tidx, c->tcoef);
-}
-
 extern "C++" template <int B>
 static void launch_collide_adj_b(boltz_ctx* c, bool table, const float* hs, const double* lo, double* ls,
                                  uint32_t s32, uint32_t flags, hipStream_t st) {
-  const bool fixed = c->adj_fixed[table ? 1 : 0];
-  if (table) {
-    if (fixed) launch_collide_adj_v<B, true, true>(c, hs, lo, ls, s32, flags, st);
-    else launch_collide_adj_v<B, true, false>(c, hs, lo, ls, s32, flags, st);
+  const int t = table ? 1 : 0;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, c->P, hs, lo, ls, s32,
+                       flags, c->tidx, c->tcoef);
+  };
+  if (c->n[2] % 4 == 0) {
+    if (table) go(collide_adj_kernel<B, true, 4>);
+    else go(collide_adj_kernel<B, false, 4>);
   } else {
-    if (fixed) launch_collide_adj_v<B, false, true>(c, hs, lo, ls, s32, flags, st);
-    else launch_collide_adj_v<B, false, false>(c, hs, lo, ls, s32, flags, st);
+    if (table) go(collide_adj_kernel<B, true, 1>);
+    else go(collide_adj_kernel<B, false, 1>);
   }
 }
 
@@ -1222,8 +1216,10 @@ static int launch_collide_adj(boltz_ctx* c, const float* hs, const double* lo, d
   const uint32_t s32 = (uint32_t)step;
   const bool table = c->ngroups > 0;
   launch_samples(c, s32, st);
-  if (c->adj_block == 256) launch_collide_adj_b<256>(c, table, hs, lo, ls, s32, flags, st);
-  else launch_collide_adj_b<512>(c, table, hs, lo, ls, s32, flags, st);
+  const int block = c->adj_block[table ? 1 : 0];
+  if (block == 256) launch_collide_adj_b<256>(c, table, hs, lo, ls, s32, flags, st);
+  else if (block == 512) launch_collide_adj_b<512>(c, table, hs, lo, ls, s32, flags, st);
+  else launch_collide_adj_b<1024>(c, table, hs, lo, ls, s32, flags, st);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "collide adjoint launch");
 }
