@@ -5,7 +5,7 @@
 //   collide_adj_kernel  S3-S5 (forward recomputed per cell in LDS)
 //   wall_adj_kernel     S1    adjoint of the face densities n_w and of the
 //                             re-emitted ghosts, wall-parameter partials
-//   sweep_adj_kernel    S2    Beam-Warming sweep transposed (order 2)
+//   stream_adj_kernel   S2    Beam-Warming sweeps transposed (order 2)
 //   order1_adj_kernel   S2    first-order unsplit step transposed
 //   lid_adj_kernel      S6    adjoint of the lid shear D
 //   grad_reduce_kernel        per-face partials -> parameter gradient
@@ -543,13 +543,53 @@ __device__ __forceinline__ double face_tau(const Params& P, const WallArgs& W, i
   return wall == WALL_BOTTOM ? P.tau_b[pos] : W.tau[wall];
 }
 
+// Coefficients of the transposed Beam-Warming sweep of one node along one
+// axis: li_i = a0 lo_i + a1 lo_{i+s} + a2 lo_{i+2s}, s the sign of v.
+struct SweepAdj {
+  double a0, a1, a2, C, an;
+  int s;
+  __device__ __forceinline__ SweepAdj(double v, double dt, double dl) {
+    an = fabs(v);
+    C = an * dt / dl;
+    const double c2 = 0.5 * C * (1.0 - C);
+    a0 = (1.0 - C) - c2;
+    a1 = C + 2.0 * c2;
+    a2 = -c2;
+    s = v > 0.0 ? 1 : -1;
+    if (v == 0.0) { a0 = 1.0; a1 = 0.0; a2 = 0.0; }
+  }
+};
+
+// Adjoint of the gas-side face value (of an outgoing node of weight w) of
+// face f of the wall a node with v != 0 leaves through: dJ/dn_w eps |v_n| w / D.
+__device__ __forceinline__ double face_adj(const Params& P, const double* lnw, int f, double an, double w) {
+  int wall, pos;
+  face_of(P, f, wall, pos);
+  return lnw[f] * P.eps * an * w / wall_consts(P, wall, pos)[1];
+}
+
+// Face term of the y sweep at (ix, iy) for a node leaving in y (order 2):
+// hhat = h_a + (1 - C)(h_a - h_a')/2 at the two cells next to the wall.
+__device__ __forceinline__ double y_face_term(const Params& P, const double* lnw, int ix, int iy, const SweepAdj& y,
+                                              double w) {
+  const int ia = y.s < 0 ? 0 : P.ny - 1, ib = y.s < 0 ? 1 : P.ny - 2;
+  if (iy != ia && iy != ib) return 0.0;
+  const double lh = face_adj(P, lnw, 2 * P.ny + (y.s < 0 ? 0 : P.nx) + ix, y.an, w);
+  double t = 0.0;
+  if (iy == ia) t += lh * (1.0 + 0.5 * (1.0 - y.C));
+  if (iy == ib) t += -lh * 0.5 * (1.0 - y.C);
+  return t;
+}
+
 // One workgroup per face f = f0 + (its index): lam is the adjoint of the
-// output of the streaming pass that read the face's ghosts (the y sweep for
-// y faces of order 2, the x sweep for x faces, the unsplit step for order
-// 1).  For the incoming nodes (v . n > 0) the ghost h_w = (n_w R - 1)/eps
-// enters the sweep with weight a1 + a2 at the adjacent cell and a2 at the
-// next one (order 2: both ghost layers), or C (order 1); with lg_j its
-// adjoint,
+// output of the streaming pass that read the face's ghosts.  PHASE 0: lam as
+// given (the y faces of order 2, every face of order 1); PHASE 1: the x faces
+// of order 2, whose sweep's output is the y sweep's input, so lam is taken
+// through the transposed y sweep (with the y faces' terms, whose lnw the
+// launch before wrote) at the two cells next to the face.  For the incoming
+// nodes (v . n > 0) the ghost h_w = (n_w R - 1)/eps enters the sweep with
+// weight a1 + a2 at the adjacent cell and a2 at the next one (order 2: both
+// ghost layers), or C (order 1); with lg_j its adjoint,
 //   dJ/dn_w   = sum_in lg_j R_j / eps
 //   dJ/dtheta = n_w sum_in lg_j dR_j/dtheta / eps
 //               - dJ/dn_w (n_w / D) sum_in |v_n| w_j dR_j/dtheta,
@@ -557,8 +597,12 @@ __device__ __forceinline__ double face_tau(const Params& P, const WallArgs& W, i
 // the mirror images of the outgoing nodes, which are the incoming ones).
 // Writes lnw[f] and the partials gpart[2f] (lid velocity, top faces only)
 // and gpart[2f + 1] (the face's temperature).
-constexpr int kWallAdjBlock = 256;
+// Latency bound: the incoming nodes only (a range of the normal axis), four
+// per thread with their loads in flight together, 1024 threads (64x64 cavity,
+// 20^3: 13 and 16 us a launch, 25..37 with 256 threads and one node at a time).
+constexpr int kWallAdjBlock = 1024;
 
+template <int PHASE>
 __global__ __launch_bounds__(kWallAdjBlock) void wall_adj_kernel(Params P, WallArgs W, const double* __restrict__ lam,
                                                                  double* __restrict__ lnw, double* __restrict__ gpart,
                                                                  int f0, int nface, int per_xcd) {
@@ -584,32 +628,75 @@ __global__ __launch_bounds__(kWallAdjBlock) void wall_adj_kernel(Params P, WallA
   const double dl = nax ? P.dy : P.dx;
   const double U = (wall == WALL_TOP) ? W.lid_u : 0.0;
   const double tau = face_tau(P, W, wall, pos);
+  const bool periodic = P.bc == 1;
+  const int64_t rowstep = (int64_t)nx * nv;
+  // incoming nodes: v > 0 at the left / bottom wall, v < 0 at the others
+  const int i0 = sgn > 0 ? P.vpos[nax] : 0, i1 = sgn > 0 ? P.n[nax] : P.vneg[nax];
+  const int c0 = nax ? P.n[0] : i1 - i0, c1 = nax ? i1 - i0 : n1, nt = c0 * c1 * n2;
   double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  NodeWalk walk(threadIdx.x, kWallAdjBlock, n1, n2);
-  for (int j = threadIdx.x; j < nv; j += kWallAdjBlock, walk.next()) {
-    const int jx = walk.jx, jy = walk.jy, jz = walk.jz;
-    const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy], v3 = P.vtab[2 * kMaxAxis + jz];
-    const double vn = nax ? v2 : v1;
-    if (!(sgn * vn > 0.0)) continue;  // incoming nodes only
-    const double an = fabs(vn);
-    const double C = an * P.dt / dl;
-    double lg;
-    if (P.order == 2) {
-      const double c2 = 0.5 * C * (1.0 - C);
-      const double a1 = C + 2.0 * c2, a2 = -c2;
-      lg = (a1 + a2) * la[j] + a2 * lb[j];
-    } else {
-      lg = C * la[j];
+  constexpr int NU = PHASE == 1 ? 2 : 4;  // nodes per thread and pass
+  if (nt > 0) {
+    NodeWalk walk((int)threadIdx.x, kWallAdjBlock, c1, n2);
+    for (int tb = threadIdx.x; tb < nt; tb += NU * kWallAdjBlock) {
+      double va[NU], vb[NU], Rj[NU], a1[NU], a2[NU], b1[NU], b2[NU];
+      int jxs[NU], jys[NU], jzs[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const bool in = tb + u * kWallAdjBlock < nt;
+        jxs[u] = in ? walk.jx + (nax ? 0 : i0) : 0;
+        jys[u] = in ? walk.jy + (nax ? i0 : 0) : 0;
+        jzs[u] = in ? walk.jz : 0;
+        walk.next();
+        const int j = (jxs[u] * n1 + jys[u]) * n2 + jzs[u];
+        va[u] = la[j];
+        vb[u] = P.order == 2 ? lb[j] : 0.0;
+        Rj[u] = R[j];
+        a1[u] = a2[u] = b1[u] = b2[u] = 0.0;
+        if (PHASE == 1) {
+          // the two cells downstream in y of each (zero beyond a wall; only
+          // cavities have faces)
+          const int sy = jys[u] < P.vneg[1] ? -1 : 1;
+          const int y1 = pos + sy, y2 = pos + 2 * sy;
+          const bool in1 = y1 >= 0 && y1 < ny, in2 = y2 >= 0 && y2 < ny;
+          if (in1) { a1[u] = la[j + sy * rowstep]; b1[u] = lb[j + sy * rowstep]; }
+          if (in2) { a2[u] = la[j + 2 * sy * rowstep]; b2[u] = lb[j + 2 * sy * rowstep]; }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (tb + u * kWallAdjBlock >= nt) continue;
+        const int jx = jxs[u], jy = jys[u], jz = jzs[u];
+        const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy], v3 = P.vtab[2 * kMaxAxis + jz];
+        const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
+        double xa = va[u], xb = vb[u];
+        if (PHASE == 1) {
+          const SweepAdj y(v2, P.dt, P.dy);
+          xa = fma(y.a0, xa, fma(y.a1, a1[u], y.a2 * a2[u]));
+          xb = fma(y.a0, xb, fma(y.a1, b1[u], y.a2 * b2[u]));
+          if (!periodic && v2 != 0.0) {
+            xa += y_face_term(P, lnw, ax_, pos, y, w);
+            xb += y_face_term(P, lnw, bx_, pos, y, w);
+          }
+        }
+        const double an = fabs(nax ? v2 : v1);
+        const double C = an * P.dt / dl;
+        double lg;
+        if (P.order == 2) {
+          const double c2 = 0.5 * C * (1.0 - C);
+          lg = ((C + 2.0 * c2) + -c2) * xa + -c2 * xb;
+        } else {
+          lg = C * xa;
+        }
+        double dU, dT;
+        wall_ratio_grad(Rj[u], v1, v2, v3, U, tau, dU, dT);
+        const double aw = an * w;
+        s[0] += lg * Rj[u];
+        s[1] += lg * dU;
+        s[2] += lg * dT;
+        s[3] += aw * dU;
+        s[4] += aw * dT;
+      }
     }
-    const double Rj = R[j];
-    double dU, dT;
-    wall_ratio_grad(Rj, v1, v2, v3, U, tau, dU, dT);
-    const double aw = an * ((P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz]);
-    s[0] += lg * Rj;
-    s[1] += lg * dU;
-    s[2] += lg * dT;
-    s[3] += aw * dU;
-    s[4] += aw * dT;
   }
   block_sum<5>(s, red);
   if (threadIdx.x == 0) {
@@ -624,74 +711,170 @@ __global__ __launch_bounds__(kWallAdjBlock) void wall_adj_kernel(Params P, WallA
 }
 
 // ---------------------------------------------------------- streaming --
-// Transposed Beam-Warming sweep along axis AX (0: x, 1: y) of order 2:
-// out_i = a0 in_i + a1 in_{i-s} + a2 in_{i-2s} gives
-//   li_i = a0 lo_i + a1 lo_{i+s} + a2 lo_{i+2s}
-// over the downstream cells inside the cavity (wrapped when periodic; the
-// ghost terms were taken by wall_adj_kernel), plus, at the two cells next to
-// each wall across AX, the adjoint of that wall's face density through the
-// gas-side face value hhat = h_a + (1 - C)(h_a - h_a')/2 of its outgoing
-// nodes: dJ/dhhat_j = dJ/dn_w eps |v_n| w_j / D.  One workgroup: one line of
-// cells along AX and 256 consecutive velocities; each thread walks its line
-// against its node's direction with a two-value register window, so every
-// element is read and written once.
-constexpr int kSweepAdjBlock = 256;
+// Transposed Beam-Warming step of order 2, y sweep then x sweep, in one pass
+// over memory (out_i = a0 in_i + a1 in_{i-s} + a2 in_{i-2s} along an axis
+// gives li_i = a0 lo_i + a1 lo_{i+s} + a2 lo_{i+2s}, over the downstream cells
+// inside the cavity, wrapped when periodic; the ghost terms were taken by
+// wall_adj_kernel), plus, at the two cells next to each wall, the adjoint of
+// that wall's face density through the gas-side face value of its outgoing
+// nodes.  One workgroup: kATX x kATY cells and 16 velocities (128 B a cell),
+// staged with their downstream halo in LDS; a thread owns V velocities of one
+// row of cells, forms the y-swept values of its row's columns (two halo
+// columns included) in registers and applies the x sweep from that window,
+// the same sums in the same order as one sweep after the other.  V = 2 where
+// nv_z is even (a pair then shares its signs and coefficients), else 1.
+// HBM bound: 16 B a node against 32 for two sweeps (64x64 cavity, 20^3:
+// 147 us, 3.6 TB/s; 94 + 107 us before).  Workgroup order as in stream4.
+constexpr int kATX = 8, kATY = 16, kAJ = 16;
 
-template <int AX>
-__global__ __launch_bounds__(kSweepAdjBlock) void sweep_adj_kernel(Params P, const double* __restrict__ lo,
-                                                                   double* __restrict__ li,
-                                                                   const double* __restrict__ lnw, int nchunks,
-                                                                   int per_xcd) {
-  const int nlines = AX == 0 ? P.ny : P.nx;
-  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (unit >= nlines * nchunks) return;
-  const int line = unit / nchunks, chunk = unit - (unit / nchunks) * nchunks;
-  const int nv = P.nv, n1 = P.n[1], n2 = P.n[2];
-  const int j = chunk * kSweepAdjBlock + threadIdx.x;
-  if (j >= nv) return;
-  int jx, jy, jz;
-  node_decode(j, n1, n2, jx, jy, jz);
-  const int n = AX == 0 ? P.nx : P.ny;
-  const int64_t stride = AX == 0 ? (int64_t)nv : (int64_t)P.nx * nv;
-  const int64_t base = (AX == 0 ? cell_off(P, 0, line) : cell_off(P, line, 0)) + j;
-  const double v = AX == 0 ? P.vtab[jx] : P.vtab[kMaxAxis + jy];
-  const double an = fabs(v);
-  const double C = an * P.dt / (AX == 0 ? P.dx : P.dy);
-  const double c2 = 0.5 * C * (1.0 - C);
-  double a0 = (1.0 - C) - c2, a1 = C + 2.0 * c2, a2 = -c2;
-  const int s = v > 0.0 ? 1 : -1;
-  if (v == 0.0) { a0 = 1.0; a1 = 0.0; a2 = 0.0; }
-  const bool periodic = P.bc == 1;
-  // face term of the wall on the outgoing side of this node
-  double fa = 0.0, fb = 0.0;
-  int ia = -1, ib = -1;
-  if (!periodic && v != 0.0) {
-    const int f = (AX == 0 ? (s < 0 ? 0 : P.ny) : 2 * P.ny + (s < 0 ? 0 : P.nx)) + line;
-    int wall, pos;
-    face_of(P, f, wall, pos);
-    const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
-    const double lh = lnw[f] * P.eps * an * w / wall_consts(P, wall, pos)[1];
-    fa = lh * (1.0 + 0.5 * (1.0 - C));
-    fb = -lh * 0.5 * (1.0 - C);
-    ia = s < 0 ? 0 : n - 1;
-    ib = s < 0 ? 1 : n - 2;
+__host__ __device__ inline int stream_adj_group(int nv) {
+  const int nchunks = (nv + kAJ - 1) / kAJ;
+  return nchunks < kChunkGroup ? nchunks : kChunkGroup;
+}
+__host__ __device__ inline int64_t stream_adj_units(int nx, int ny, int nv) {
+  const int64_t tiles = (int64_t)((nx + kATX - 1) / kATX) * ((ny + kATY - 1) / kATY);
+  const int cg = stream_adj_group(nv);
+  return tiles * (((nv + kAJ - 1) / kAJ + cg - 1) / cg) * cg;
+}
+
+template <int V>
+struct VecD {
+  double e[V];
+};
+template <int V>
+__device__ __forceinline__ VecD<V> load_vd(const double* p) {
+  VecD<V> r;
+  if constexpr (V == 2) {
+    const f64x2 t = *reinterpret_cast<const f64x2*>(p);
+    r.e[0] = t.x;
+    r.e[1] = t.y;
+  } else {
+    r.e[0] = p[0];
   }
-  auto at = [&](int i) -> double {
-    if (i >= 0 && i < n) return lo[base + i * stride];
-    if (!periodic) return 0.0;
-    return lo[base + (int64_t)wrapi(i, n) * stride];
-  };
-  const int i0 = s > 0 ? n - 1 : 0;
-  double d1 = at(i0 + s), d2 = at(i0 + 2 * s);
-  for (int k = 0; k < n; ++k) {
-    const int i = i0 - k * s;
-    const double c0 = lo[base + i * stride];
-    double out = fma(a0, c0, fma(a1, d1, a2 * d2));
-    if (i == ia) out += fa;
-    if (i == ib) out += fb;
-    li[base + i * stride] = out;
-    d2 = d1;
-    d1 = c0;
+  return r;
+}
+template <int V>
+__device__ __forceinline__ void store_vd(double* p, const VecD<V>& v) {
+  if constexpr (V == 2) *reinterpret_cast<f64x2*>(p) = f64x2{v.e[0], v.e[1]};
+  else p[0] = v.e[0];
+}
+template <int V>
+__device__ __forceinline__ VecD<V> sweep3(const SweepAdj& c, const VecD<V>& x0, const VecD<V>& x1,
+                                          const VecD<V>& x2) {
+  VecD<V> r;
+#pragma unroll
+  for (int e = 0; e < V; ++e) r.e[e] = fma(c.a0, x0.e[e], fma(c.a1, x1.e[e], c.a2 * x2.e[e]));
+  return r;
+}
+
+template <int V>
+__global__ __launch_bounds__(kATY * (kAJ / V)) void stream_adj_kernel(Params P, const double* __restrict__ lo,
+                                                                      double* __restrict__ li,
+                                                                      const double* __restrict__ lnw, int tiles_x,
+                                                                      int tiles_y, int nunits, int per_xcd) {
+  constexpr int Q = kAJ / V, NT = kATY * Q, AX = kATX + 4, AY = kATY + 4;
+  __shared__ __align__(16) double A[AY * AX * kAJ];
+  const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (unit >= nunits) return;
+  const int nx = P.nx, ny = P.ny, nv = P.nv, n1 = P.n[1], n2 = P.n[2];
+  const int gsz = stream_adj_group(nv), per_group = tiles_x * tiles_y * gsz;
+  const int cg = unit / per_group, rem = unit - cg * per_group;
+  const int tile = rem / gsz, chunk = cg * gsz + (rem - tile * gsz);
+  if (chunk * kAJ >= nv) return;  // padding unit of the last group
+  const int ix0 = (tile % tiles_x) * kATX, iy0 = (tile / tiles_x) * kATY, j0 = chunk * kAJ;
+  const bool periodic = P.bc == 1;
+  // downstream sides that the chunk's velocities need (jx, and within one jx
+  // also jy, increase with j)
+  int fx, fy, fz, lx, ly, lz;
+  node_decode(j0, n1, n2, fx, fy, fz);
+  node_decode(min(j0 + kAJ, nv) - 1, n1, n2, lx, ly, lz);
+  const bool oneX = fx == lx;
+  const bool needR = P.vtab[lx] > 0.0, needL = P.vtab[fx] < 0.0;
+  const bool needT = !oneX || P.vtab[kMaxAxis + ly] > 0.0, needB = !oneX || P.vtab[kMaxAxis + fy] < 0.0;
+  const int c_lo = needL ? 0 : 2, c_hi = needR ? AX : AX - 2;
+  const int r_lo = needB ? 0 : 2, r_hi = needT ? AY : AY - 2;
+  const int q = threadIdx.x % Q, jq = j0 + V * q;
+  {
+    // all loads of a thread are issued before its LDS stores
+    constexpr int kRows = NT / Q, kIter = (AY * AX + kRows - 1) / kRows;
+    VecD<V> v[kIter];
+#pragma unroll
+    for (int it = 0; it < kIter; ++it) {
+      const int cidx = (int)threadIdx.x / Q + it * kRows;
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[it].e[e] = 0.0;
+      if (cidx >= AY * AX) continue;
+      const int r = cidx / AX, c = cidx - r * AX;
+      if (r < r_lo || r >= r_hi || c < c_lo || c >= c_hi || jq >= nv) continue;
+      const int iy = iy0 - 2 + r, ix = ix0 - 2 + c;
+      if (periodic) v[it] = load_vd<V>(lo + cell_off(P, wrapi(ix, nx), wrapi(iy, ny)) + jq);
+      else if (ix >= 0 && ix < nx && iy >= 0 && iy < ny) v[it] = load_vd<V>(lo + cell_off(P, ix, iy) + jq);
+    }
+#pragma unroll
+    for (int it = 0; it < kIter; ++it) {
+      const int cidx = (int)threadIdx.x / Q + it * kRows;
+      if (cidx < AY * AX) store_vd<V>(&A[cidx * kAJ + V * q], v[it]);
+    }
+  }
+  const int r = (int)threadIdx.x / Q, iy = iy0 + r;
+  const bool ok = jq < nv && iy < ny;
+  int jx = 0, jy = 0;
+  if (jq < nv) {
+    const int row = div_small(jq, n2);
+    jx = div_small(row, n1);
+    jy = row - jx * n1;
+  }
+  const double vx = P.vtab[jx], vy = P.vtab[kMaxAxis + jy];
+  const SweepAdj sx(vx, P.dt, P.dx), sy(vy, P.dt, P.dy);
+  double w[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e)
+    w[e] = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + (jq < nv ? jq + e - (jx * n1 + jy) * n2 : 0)];
+  __syncthreads();
+  if (!ok) return;
+  // rows next to the wall that the node leaves through in y
+  const bool yface = !periodic && vy != 0.0 && (sy.s < 0 ? iy <= 1 : iy >= ny - 2);
+  VecD<V> t[AX];
+#pragma unroll
+  for (int c = 0; c < AX; ++c) {
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[c].e[e] = 0.0;
+    if (c < c_lo || c >= c_hi) continue;
+    const int ix = ix0 - 2 + c;
+    if (!periodic && (ix < 0 || ix >= nx)) continue;
+    const double* col = &A[((r + 2) * AX + c) * kAJ + V * q];
+    t[c] = sweep3<V>(sy, load_vd<V>(col), load_vd<V>(col + sy.s * AX * kAJ), load_vd<V>(col + 2 * sy.s * AX * kAJ));
+    if (yface) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) t[c].e[e] += y_face_term(P, lnw, ix, iy, sy, w[e]);
+    }
+  }
+  // the wall that the node leaves through in x
+  const bool xface = !periodic && vx != 0.0;
+  const int ia = sx.s < 0 ? 0 : nx - 1, ib = sx.s < 0 ? 1 : nx - 2;
+#pragma unroll
+  for (int c = 0; c < kATX; ++c) {
+    const int ix = ix0 + c;
+    if (ix >= nx) break;
+    VecD<V> x1, x2;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      x1.e[e] = sx.s > 0 ? t[c + 3].e[e] : t[c + 1].e[e];
+      x2.e[e] = sx.s > 0 ? t[c + 4].e[e] : t[c].e[e];
+    }
+    VecD<V> o = sweep3<V>(sx, t[c + 2], x1, x2);
+    if (xface && (ix == ia || ix == ib)) {
+      const int f = (sx.s < 0 ? 0 : ny) + iy;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const double lh = face_adj(P, lnw, f, sx.an, w[e]);
+        if (ix == ia) o.e[e] += lh * (1.0 + 0.5 * (1.0 - sx.C));
+        if (ix == ib) o.e[e] += -lh * 0.5 * (1.0 - sx.C);
+      }
+    }
+    double* dst = li + cell_off(P, ix, iy) + jq;
+    if constexpr (V == 2) __builtin_nontemporal_store(f64x2{o.e[0], o.e[1]}, reinterpret_cast<f64x2*>(dst));
+    else dst[0] = o.e[0];
   }
 }
 

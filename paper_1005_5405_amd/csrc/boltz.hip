@@ -779,14 +779,16 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   c->adj_supported = ea == hipSuccess && !seq && adjoint_fits(c->nv, nsum);
   for (int t = 0; t < 2 && ea == hipSuccess && c->adj_supported; ++t) {
     const int block = adjoint_block(c->nv, nsum, t == 0, c->ncells, ncu < 1 ? 1 : ncu);
-    const void* fn = collide_adj_fn(block, t == 1, c->n[2] % 4 == 0);
     c->adj_block[t] = block;
     c->adj_lds[t] = collide_adj_lds(c->nv, nsum, t == 0, block);
     // (per kernel, shared by every context: the largest size)
-    ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(kLdsBytes - collide_adj_static_lds(block)));
+    for (int v = 0; v < 2 && ea == hipSuccess; ++v)
+      ea = hipFuncSetAttribute(collide_adj_fn(block, t == 1, v == 1), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)(kLdsBytes - collide_adj_static_lds(block)));
     int per_cu = 0;
-    if (ea == hipSuccess) ea = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, block, c->adj_lds[t]);
+    if (ea == hipSuccess)
+      ea = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, collide_adj_fn(block, t == 1, c->n[2] % 4 == 0),
+                                                        block, c->adj_lds[t]);
     if (ea == hipSuccess && per_cu < 1) ea = hipErrorInvalidConfiguration;
     const int64_t cap = (int64_t)per_cu * (ncu < 1 ? 1 : ncu);
     c->adj_grid[t] = c->ncells < cap ? c->ncells : cap;
@@ -1157,34 +1159,37 @@ int boltz_moments(boltz_ctx* c, const float* h, const boltz_walls* walls, double
 
 // ------------------------------------------------------------- adjoint --
 // Reverse mode of the streaming step whose face densities P.nw are current:
-// lo (adjoint of the streamed state) -> li.  Order 2: y sweep transposed
-// into tmp, then x sweep into li (li may equal lo); order 1: li != lo.
-// Wall-parameter partials go to grad (when not NULL).
-static int launch_stream_adj(boltz_ctx* c, const WallArgs& W, const double* lo, double* li, double* tmp,
-                             double* grad, hipStream_t st) {
+// lo (adjoint of the streamed state) -> li (li != lo).  Wall-parameter
+// partials go to grad (when not NULL).
+static int launch_stream_adj(boltz_ctx* c, const WallArgs& W, const double* lo, double* li, double* grad,
+                             hipStream_t st) {
   const bool cavity = c->p.bc == BOLTZ_BC_CAVITY;
   const int nx = c->p.nx, ny = c->p.ny;
-  const int nchunks = (c->nv + kSweepAdjBlock - 1) / kSweepAdjBlock;
-  auto walls_adj = [&](const double* lam, int f0, int nface) {
+  auto walls_adj = [&](auto kern, int f0, int nface) {
     const int per_xcd = (nface + 7) / 8;
-    hipLaunchKernelGGL(wall_adj_kernel, dim3(8 * per_xcd), dim3(kWallAdjBlock), 0, st, c->P, W, lam, c->lnw,
-                       c->gpart, f0, nface, per_xcd);
-  };
-  auto sweep = [&](auto kern, const double* in, double* out, int nlines) {
-    const long long units = (long long)nlines * nchunks;
-    const int per_xcd = (int)((units + 7) / 8);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * (long long)per_xcd)), dim3(kSweepAdjBlock), 0, st, c->P, in, out,
-                       c->lnw, nchunks, per_xcd);
+    hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(kWallAdjBlock), 0, st, c->P, W, lo, c->lnw, c->gpart, f0, nface,
+                       per_xcd);
   };
   if (c->p.order == 2) {
-    // y faces and the y sweep read the adjoint of the y-sweep output; the x
-    // faces and the x sweep that of the x-swept state
-    if (cavity) walls_adj(lo, 2 * ny, 2 * nx);
-    sweep(sweep_adj_kernel<1>, lo, tmp, nx);
-    if (cavity) walls_adj(tmp, 0, 2 * ny);
-    sweep(sweep_adj_kernel<0>, tmp, li, ny);
+    // the x faces' terms pass through the y sweep, hence after the y faces
+    if (cavity) {
+      walls_adj(wall_adj_kernel<0>, 2 * ny, 2 * nx);
+      walls_adj(wall_adj_kernel<1>, 0, 2 * ny);
+    }
+    const int tiles_x = (nx + kATX - 1) / kATX, tiles_y = (ny + kATY - 1) / kATY;
+    const long long units = stream_adj_units(nx, ny, c->nv);
+    const int per_xcd = (int)((units + 7) / 8);
+    const dim3 grid((unsigned)(8 * (long long)per_xcd));
+    // pairs of velocities need rows of even length and 16-byte aligned buffers
+    const bool pairs = c->n[2] % 2 == 0 && ((reinterpret_cast<uintptr_t>(lo) | reinterpret_cast<uintptr_t>(li)) & 15) == 0;
+    if (pairs)
+      hipLaunchKernelGGL(stream_adj_kernel<2>, grid, dim3(kATY * kAJ / 2), 0, st, c->P, lo, li, c->lnw, tiles_x, tiles_y,
+                         (int)units, per_xcd);
+    else
+      hipLaunchKernelGGL(stream_adj_kernel<1>, grid, dim3(kATY * kAJ), 0, st, c->P, lo, li, c->lnw, tiles_x, tiles_y,
+                         (int)units, per_xcd);
   } else {
-    if (cavity) walls_adj(lo, 0, 2 * (nx + ny));
+    if (cavity) walls_adj(wall_adj_kernel<0>, 0, 2 * (nx + ny));
     const int nc = (c->nv + kOrder1AdjBlock - 1) / kOrder1AdjBlock;
     hipLaunchKernelGGL(order1_adj_kernel, dim3((unsigned)(c->ncells * nc)), dim3(kOrder1AdjBlock), 0, st, c->P, lo,
                        li, c->lnw, nc);
@@ -1202,7 +1207,8 @@ static void launch_collide_adj_b(boltz_ctx* c, bool table, const float* hs, cons
     hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, c->P, hs, lo, ls, s32,
                        flags, c->tidx, c->tcoef);
   };
-  if (c->n[2] % 4 == 0) {
+  // four nodes per access: whole quadruples per row, 16-byte aligned buffers
+  if (c->n[2] % 4 == 0 && ((reinterpret_cast<uintptr_t>(lo) | reinterpret_cast<uintptr_t>(ls)) & 15) == 0) {
     if (table) go(collide_adj_kernel<B, true, 4>);
     else go(collide_adj_kernel<B, false, 4>);
   } else {
@@ -1212,10 +1218,10 @@ static void launch_collide_adj_b(boltz_ctx* c, bool table, const float* hs, cons
 }
 
 static int launch_collide_adj(boltz_ctx* c, const float* hs, const double* lo, double* ls, int64_t step,
-                              uint32_t flags, hipStream_t st) {
+                              uint32_t flags, hipStream_t st, bool drawn = false) {
   const uint32_t s32 = (uint32_t)step;
   const bool table = c->ngroups > 0;
-  launch_samples(c, s32, st);
+  if (!drawn) launch_samples(c, s32, st);
   const int block = c->adj_block[table ? 1 : 0];
   if (block == 256) launch_collide_adj_b<256>(c, table, hs, lo, ls, s32, flags, st);
   else if (block == 512) launch_collide_adj_b<512>(c, table, hs, lo, ls, s32, flags, st);
@@ -1241,7 +1247,7 @@ int boltz_stream_adjoint(boltz_ctx* c, const float* h_in, const double* lam_out,
   const WallArgs W = make_walls(walls);
   int rc = BOLTZ_OK;
   if (cavity) rc = launch_walls(c, h_in, W, walls, st);
-  if (rc == BOLTZ_OK) rc = launch_stream_adj(c, W, lam_out, lam_in, c->adj_lam, grad_walls, st);
+  if (rc == BOLTZ_OK) rc = launch_stream_adj(c, W, lam_out, lam_in, grad_walls, st);
   return rc;
 }
 
@@ -1274,20 +1280,15 @@ int boltz_step_adjoint(boltz_ctx* c, const float* h_in, const double* lam_out, d
     return fail(c, BOLTZ_EINVAL, "boltz_step_adjoint: cavity needs valid walls");
   hipStream_t st = static_cast<hipStream_t>(stream);
   const WallArgs W = make_walls(walls);
-  // forward streaming again (also leaves the face densities of h_in in P.nw)
+  // forward streaming again (also leaves the face densities of h_in in P.nw),
+  // the step's pair records drawn in its face launch as in boltz_step
   int rc = BOLTZ_OK;
-  if (cavity) rc = launch_walls(c, h_in, W, walls, st);
+  if (cavity) rc = launch_walls(c, h_in, W, walls, st, step);
+  const bool drawn = cavity && step >= 0 && samples_with_walls(c);
   if (rc == BOLTZ_OK) rc = launch_stream(c, h_in, c->adj_hs, st);
   if (rc != BOLTZ_OK) return rc;
-  if (c->p.order == 2) {
-    // collision adjoint into lam_in (in place when it is lam_out), then the
-    // sweeps through the scratch back into lam_in
-    rc = launch_collide_adj(c, c->adj_hs, lam_out, lam_in, step, 0u, st);
-    if (rc == BOLTZ_OK) rc = launch_stream_adj(c, W, lam_in, lam_in, c->adj_lam, grad_walls, st);
-  } else {
-    rc = launch_collide_adj(c, c->adj_hs, lam_out, c->adj_lam, step, 0u, st);
-    if (rc == BOLTZ_OK) rc = launch_stream_adj(c, W, c->adj_lam, lam_in, nullptr, grad_walls, st);
-  }
+  rc = launch_collide_adj(c, c->adj_hs, lam_out, c->adj_lam, step, 0u, st, drawn);
+  if (rc == BOLTZ_OK) rc = launch_stream_adj(c, W, c->adj_lam, lam_in, grad_walls, st);
   return rc;
 }
 
