@@ -148,6 +148,26 @@ std::vector<double> bottom_taus(const boltz_walls* w, int nx) {
   return t;
 }
 
+// {S, C} of cos_sin_2pi (device_math.hpp) for the arguments z = (i + 1/2) /
+// 8192 * pi / 4, i < 8192, with its operations in its order (FP contraction
+// is off on both sides), so the device reads the bits it would compute.
+const std::vector<double>& octant_table() {
+  static const std::vector<double> tab = [] {
+    std::vector<double> t(2 * 8192);
+    for (int i = 0; i < 8192; ++i) {
+      const double z = ((i + 0.5) * 0x1p-13) * kPiOver4, z2 = z * z;
+      double ps = 1.0 / 6227020800.0;
+      for (double a : {-1.0 / 39916800.0, 1.0 / 362880.0, -1.0 / 5040.0, 1.0 / 120.0, -1.0 / 6.0, 1.0}) ps = a + z2 * ps;
+      double pc = 1.0 / 479001600.0;
+      for (double a : {-1.0 / 3628800.0, 1.0 / 40320.0, -1.0 / 720.0, 1.0 / 24.0, -1.0 / 2.0}) pc = a + z2 * pc;
+      t[2 * i] = z * ps;
+      t[2 * i + 1] = 1.0 + z2 * pc;
+    }
+    return t;
+  }();
+  return tab;
+}
+
 constexpr size_t kLdsBytes = 160 * 1024;
 
 // static LDS of the collide kernel (block reduction scratch and flags) per
@@ -513,11 +533,10 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   c->qfac = (p->n_pairs > 0) ? (c->dt * c->K) / (double)p->n_pairs : 0.0;
 
   // ---- host images of the device tables
-  std::vector<double> vtab(3 * kMaxAxis, 0.0), omtab(3 * kMaxAxis, 0.0), rwtab(3 * kMaxAxis, 0.0);
+  std::vector<double> vtab(3 * kMaxAxis, 0.0), omtab(3 * kMaxAxis, 0.0);
   std::vector<double> edgetab(3 * (kMaxAxis + 1), 0.0);
   for (int k = 0; k < 3; ++k)
     for (int i = 0; i <= c->n[k]; ++i) edgetab[k * (kMaxAxis + 1) + i] = c->edge[k][i];
-  std::vector<float4> nqtab(3 * kMaxAxis, make_float4(0.f, 0.f, 0.f, 0.f));
   std::vector<uint8_t> icdf(3 * kFieldSize, 0);
   std::vector<float> cour(2 * kMaxAxis, 0.f), cour2(2 * kMaxAxis, 0.f);
   // omega_z v_z^p (p = 0..4) per z node, eight doubles a node
@@ -532,9 +551,6 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
     for (int i = 0; i < n; ++i) {
       vtab[k * kMaxAxis + i] = c->v[k][i];
       omtab[k * kMaxAxis + i] = c->om[k][i];
-      rwtab[k * kMaxAxis + i] = 1.0 / c->om[k][i];
-      nqtab[k * kMaxAxis + i] =
-          make_float4((float)c->om[k][i], (float)c->pphi[k][i], (float)c->punif[k][i], 0.f);
     }
     // direct inverse CDF of the Maxwellian law: icdf[f] = #{i >= 1 : T_i <= f}
     int idx = 0;
@@ -543,6 +559,30 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
       icdf[k * kFieldSize + f] = (uint8_t)idx;
     }
   }
+  // per node: 1 / w, and the importance weights of a draw in FP32
+  std::vector<double> rwnode((size_t)c->nv);
+  std::vector<float2> nwtab((size_t)c->nv);
+  {
+    const float beta = (float)(p->mix16 / 16.0), obeta = 1.0f - beta;
+    size_t j = 0;
+    for (int ix = 0; ix < c->n[0]; ++ix)
+      for (int iy = 0; iy < c->n[1]; ++iy)
+        for (int iz = 0; iz < c->n[2]; ++iz, ++j) {
+          const int i[3] = {ix, iy, iz};
+          double rw = 1.0;
+          float w = 1.0f, pm = 1.0f, pu = 1.0f;
+          for (int k = 0; k < 3; ++k) {
+            rw *= 1.0 / c->om[k][i[k]];
+            w *= (float)c->om[k][i[k]];
+            pm *= (float)c->pphi[k][i[k]];
+            pu *= (float)c->punif[k][i[k]];
+          }
+          rwnode[j] = rw;
+          const float sp = 1.0f / (obeta * pm + beta * pu);
+          nwtab[j] = make_float2(w * sp, sp);
+        }
+  }
+  const std::vector<double>& sctab = octant_table();
   // M0 = sum_j w_j psi_k psi_l, psi = (1, v_x, v_y, v_z, |v|^2), packed k <= l
   std::vector<double> m0(16, 0.0);
   for (int ix = 0; ix < c->n[0]; ++ix)
@@ -563,19 +603,38 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
       cour2[k * kMaxAxis + i] = (float)(0.5 * C * (1.0 - C));
     }
   }
-  // ---- device memory: tables + scratch in one allocation
+  std::vector<double> vom(2 * (size_t)nsum, 0.0);
+  {
+    size_t i = 0;
+    for (int k = 0; k < 3; ++k)
+      for (int j = 0; j < c->n[k]; ++j, ++i) {
+        vom[i] = c->v[k][j];
+        vom[nsum + i] = c->om[k][j];
+      }
+  }
+  // stretched spatial cells: x widths, 1 / x widths, 1 / y widths
+  std::vector<double> swid;
+  if (c->sstretched) {
+    for (double w : c->wx) swid.push_back(w);
+    for (double w : c->wx) swid.push_back(1.0 / w);
+    for (double w : c->wy) swid.push_back(1.0 / w);
+  }
+  // ---- device memory: tables (first, one copy) + scratch in one allocation
   const int nfaces = 2 * (p->nx + p->ny);
   size_t off = 0;
   const size_t o_v = off; off = align256(off + vtab.size() * 8);
   const size_t o_edge = off; off = align256(off + edgetab.size() * 8);
   const size_t o_om = off; off = align256(off + omtab.size() * 8);
-  const size_t o_rw = off; off = align256(off + rwtab.size() * 8);
-  const size_t o_nq = off; off = align256(off + nqtab.size() * 16);
+  const size_t o_rw = off; off = align256(off + rwnode.size() * 8);
+  const size_t o_nq = off; off = align256(off + nwtab.size() * 8);
+  const size_t o_sc = off; off = align256(off + sctab.size() * 8);
   const size_t o_icdf = off; off = align256(off + icdf.size());
   const size_t o_m0 = off; off = align256(off + m0.size() * 8);
   const size_t o_zmom = off; off = align256(off + zmom.size() * 8);
   const size_t o_cour = off; off = align256(off + cour.size() * 4);
   const size_t o_cour2 = off; off = align256(off + cour2.size() * 4);
+  const size_t o_vom = off; off = align256(off + vom.size() * 8);
+  const size_t o_swid = off; off = align256(off + swid.size() * 8);
   const size_t o_nw = off; off = align256(off + (size_t)nfaces * 8);
   const size_t o_ratio = off; off = align256(off + (size_t)4 * c->nv * 8);
   const size_t o_ratio_b = off; off = align256(off + (size_t)p->nx * c->nv * 8);
@@ -607,24 +666,6 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   const size_t o_adj_lam = off; off = align256(off + (with_adj ? nodes * 8 : 0));
   const int64_t ngr_seq = (p->n_pairs + kSeqGroup - 1) / kSeqGroup;
   const size_t o_sched = off; off = align256(off + (seq ? SeqSched::bytes(ngr_seq, ngroups) : 0));
-  std::vector<double> vom(2 * (size_t)nsum, 0.0);
-  {
-    size_t i = 0;
-    for (int k = 0; k < 3; ++k)
-      for (int j = 0; j < c->n[k]; ++j, ++i) {
-        vom[i] = c->v[k][j];
-        vom[nsum + i] = c->om[k][j];
-      }
-  }
-  const size_t o_vom = off; off = align256(off + vom.size() * 8);
-  // stretched spatial cells: x widths, 1 / x widths, 1 / y widths
-  std::vector<double> swid;
-  if (c->sstretched) {
-    for (double w : c->wx) swid.push_back(w);
-    for (double w : c->wx) swid.push_back(1.0 / w);
-    for (double w : c->wy) swid.push_back(1.0 / w);
-  }
-  const size_t o_swid = off; off = align256(off + swid.size() * 8);
   (void)hipGetDevice(&c->device);
   hipError_t e = hipMalloc(&c->dmem, off);
   if (e != hipSuccess) {
@@ -636,17 +677,19 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   struct Cp { size_t o; const void* src; size_t n; } cps[] = {
       {o_v, vtab.data(), vtab.size() * 8}, {o_edge, edgetab.data(), edgetab.size() * 8},
       {o_om, omtab.data(), omtab.size() * 8},
-      {o_rw, rwtab.data(), rwtab.size() * 8}, {o_nq, nqtab.data(), nqtab.size() * 16},
+      {o_rw, rwnode.data(), rwnode.size() * 8}, {o_nq, nwtab.data(), nwtab.size() * 8},
+      {o_sc, sctab.data(), sctab.size() * 8},
       {o_icdf, icdf.data(), icdf.size()}, {o_m0, m0.data(), m0.size() * 8},
       {o_zmom, zmom.data(), zmom.size() * 8},
       {o_cour, cour.data(), cour.size() * 4}, {o_cour2, cour2.data(), cour2.size() * 4},
       {o_vom, vom.data(), vom.size() * 8}, {o_swid, swid.data(), swid.size() * 8}};
-  for (const Cp& cp : cps) {
-    e = hipMemcpy(base + cp.o, cp.src, cp.n, hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      boltz_destroy(c);
-      return fail(nullptr, BOLTZ_EHIP, std::string("boltz_create: hipMemcpy: ") + hipGetErrorString(e));
-    }
+  std::vector<unsigned char> image(o_nw, 0);
+  for (const Cp& cp : cps)
+    if (cp.n) std::memcpy(image.data() + cp.o, cp.src, cp.n);
+  e = hipMemcpy(base, image.data(), image.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    boltz_destroy(c);
+    return fail(nullptr, BOLTZ_EHIP, std::string("boltz_create: hipMemcpy: ") + hipGetErrorString(e));
   }
   e = hipMemset(base + o_nw, 0, o_status + 4 - o_nw);
   if (e == hipSuccess && hyb_rows) e = hipMemset(base + o_hyb, 0, (size_t)hyb_rows * (size_t)nvt * 4);
@@ -695,8 +738,9 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   P.inv_wy = c->sstretched ? P.wx + 2 * p->nx : nullptr;
   P.edgetab = reinterpret_cast<const double*>(base + o_edge);
   P.omtab = reinterpret_cast<const double*>(base + o_om);
-  P.rwtab = reinterpret_cast<const double*>(base + o_rw);
-  P.nqtab = reinterpret_cast<const float4*>(base + o_nq);
+  P.rwnode = reinterpret_cast<const double*>(base + o_rw);
+  P.nwtab = reinterpret_cast<const float2*>(base + o_nq);
+  P.sctab = reinterpret_cast<const double2*>(base + o_sc);
   P.icdf = reinterpret_cast<const uint8_t*>(base + o_icdf);
   P.m0 = reinterpret_cast<const double*>(base + o_m0);
   P.zmom = reinterpret_cast<const double*>(base + o_zmom);

@@ -11,20 +11,20 @@ namespace boltz {
 // ---------------------------------------------------------------- tables --
 // LDS copies of the per-axis tables, ns = n0 + n1 + n2 entries each:
 //   v, om, xt        always (moment sums and the correction)
-//   nq, rw, icdf     only where pairs are drawn
+//   icdf, edge       only where pairs are drawn
 struct TablesLDS {
   double* v;      // node velocities
   double* om;     // omega, FP64
   double* xt;     // per-axis parts of x . psi of the correction (per cell)
   double* m0;     // [16] sum_j w_j psi_k psi_l (packed k <= l), constant
-  float4* nq;     // {omega, p_phi, p_unif, 0}, FP32
-  double* rw;     // 1 / omega, FP64
   uint8_t* icdf;  // [3 * kFieldSize] Maxwellian inverse CDF on 12-bit fields
   double* edge;   // [ns + 3] cell edges per axis (n + 1 each), for the search
                   // of post-collision cells on stretched grids
 
   static __host__ __device__ size_t bytes(int ns, bool sampler) {
     size_t b = 24 * (size_t)ns + 16 * sizeof(double);
+    // (the layouts' limits were set with 32 bytes per entry here; the tables
+    // now take 8 of them)
     if (sampler) b += 32 * (size_t)ns + 24 + 3 * (size_t)kFieldSize;
     return b;
   }
@@ -37,19 +37,13 @@ __device__ __forceinline__ void load_tables(const Params& P, unsigned char* base
   T.om = T.v + ns;
   T.xt = T.om + ns;
   T.m0 = T.xt + ns;
-  T.nq = reinterpret_cast<float4*>(T.m0 + 16);
-  T.rw = reinterpret_cast<double*>(T.nq + ns);
-  T.edge = T.rw + ns;
+  T.edge = T.m0 + 16;
   T.icdf = reinterpret_cast<uint8_t*>(T.edge + ns + 3);
   for (int i = threadIdx.x; i < ns; i += blockDim.x) {
     const int k = i < n0 ? 0 : (i < n0 + n1 ? 1 : 2);
     const int o = k * kMaxAxis + i - (k == 0 ? 0 : (k == 1 ? n0 : n0 + n1));
     T.v[i] = P.vtab[o];
     T.om[i] = P.omtab[o];
-    if (sampler) {
-      T.nq[i] = P.nqtab[o];
-      T.rw[i] = P.rwtab[o];
-    }
   }
   if (sampler) {
     // n + 1 edges per axis, axis k at offset n0 + ... + n_{k-1} + k
@@ -68,24 +62,36 @@ __device__ __forceinline__ void load_tables(const Params& P, unsigned char* base
 }
 
 // ----------------------------------------------------------------- S3 --
-// Importance weights of a drawn node (i, j, k): r = w / p~ and s = 1 / p~,
-// with w the midpoint weight of Phi0 and p~ = (1 - beta) p_phi + beta p_unif
-// the probability of drawing it from the mixture law.  FP32.
-struct NodeWeight {
-  float r, s;
-};
+// Square root of x in [2^-40, 1], correctly rounded: the hardware estimate of
+// 1 / sqrt(x) refined by Goldschmidt's coupled iteration, then two residual
+// corrections, without the range scaling and special cases of the general
+// function (x is a product of two exact factors in (2^-32, 2)).
+__device__ __forceinline__ double sqrt_unit(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  h = fma(h, r, h);
+  g = fma(g, r, g);
+  g = fma(fma(-g, g, x), h, g);
+  return fma(fma(-g, g, x), h, g);
+}
 
-__device__ __forceinline__ NodeWeight node_weight(const TablesLDS& T, float beta, float obeta, int i, int j, int k,
-                                                  int n0, int n1) {
-  const float4 x = T.nq[i], y = T.nq[n0 + j], z = T.nq[n0 + n1 + k];
-  const float w = (x.x * y.x) * z.x;
-  const float pm = (x.y * y.y) * z.y;
-  const float pu = (x.z * y.z) * z.z;
-  const float s = 1.0f / (obeta * pm + beta * pu);
-  NodeWeight o;
-  o.r = w * s;
-  o.s = s;
-  return o;
+// (cos, sin) of the azimuth 2 pi (phi + 1/2) 2^-16 of a 16-bit phi, the values
+// of cos_sin_2pi: its polynomials (S, C) on the 8192 arguments of one octant
+// come from a table of the context (128 KB, L2 resident), then the octant's
+// exchange and signs.  Six LDS table reads, two FP32 divisions and 26
+// polynomial steps per pair gave way to five gathers through the vector memory
+// path, which the pair loop leaves idle (the LDS and the vector issue bound it;
+// see node_weight in sample_pair_node).
+__device__ __forceinline__ void azimuth16(const double2* __restrict__ sctab, uint32_t phi, double& cs, double& sn) {
+  const uint32_t oct = phi >> 13;
+  const uint32_t i = (phi & 8191u) ^ ((oct & 1u) ? 8191u : 0u);
+  const double2 sc = sctab[i];  // {S, C}
+  const bool swap = (((oct + 1u) >> 1) & 1u) != 0u;
+  const double c0 = swap ? sc.x : sc.y, s0 = swap ? sc.y : sc.x;
+  const int cneg = (int)(((oct + 2u) << 29) & 0x80000000u), sneg = (int)((oct << 29) & 0x80000000u);
+  cs = __hiloint2double(__double2hiint(c0) ^ cneg, __double2loint(c0));
+  sn = __hiloint2double(__double2hiint(s0) ^ sneg, __double2loint(s0));
 }
 
 // Cell of x among n stretched cells with edges e[0] = -a < ... < e[n] = a:
@@ -149,12 +155,17 @@ __device__ __forceinline__ Pair sample_pair_node(const Params& P, const TablesLD
   const int iby = ub ? uniform_draw(fby, n1) : mby;
   const int ibz = ub ? uniform_draw(fbz, n2) : mbz;
   const uint32_t phi = ((r.y & 0xFFu) << 8) | (r.z & 0xFFu);
-  const double u6 = ((double)r.w + 0.5) * 0x1p-32;
-  const double u7 = ((double)phi + 0.5) * 0x1p-16;
-  const double kz = 2.0 * u6 - 1.0;
-  const double s = sqrt((1.0 - kz) * (1.0 + kz));
   double cp, sp;
-  cos_sin_2pi(u7, cp, sp);
+  azimuth16(P.sctab, phi, cp, sp);
+  Pair p;
+  p.a = node_index(iax, iay, iaz, n1, n2);
+  p.b = node_index(ibx, iby, ibz, n1, n2);
+  // importance weights of the drawn nodes, {w / p~, 1 / p~}, from the
+  // context's per-node table
+  const float2 wa = P.nwtab[p.a], wb = P.nwtab[p.b];
+  const double u6 = ((double)r.w + 0.5) * 0x1p-32;
+  const double kz = 2.0 * u6 - 1.0;
+  const double s = sqrt_unit((1.0 - kz) * (1.0 + kz));
   const double kx = s * cp, ky = s * sp;
   const double* vx = T.v;
   const double* vy = T.v + n0;
@@ -194,22 +205,17 @@ __device__ __forceinline__ Pair sample_pair_node(const Params& P, const TablesLD
   }
   const bool kept = ((unsigned)sx < (unsigned)n0) & ((unsigned)sy < (unsigned)n1) & ((unsigned)sz < (unsigned)n2) &
                     ((unsigned)tx < (unsigned)n0) & ((unsigned)ty < (unsigned)n1) & ((unsigned)tz < (unsigned)n2);
-  Pair p;
-  p.a = (iax * n1 + iay) * n2 + iaz;
-  p.b = (ibx * n1 + iby) * n2 + ibz;
   if (kept) {
-    p.as = (sx * n1 + sy) * n2 + sz;
-    p.bs = (tx * n1 + ty) * n2 + tz;
-    const float beta = (float)P.beta;
-    const NodeWeight wa = node_weight(T, beta, 1.0f - beta, iax, iay, iaz, n0, n1);
-    const NodeWeight wb = node_weight(T, beta, 1.0f - beta, ibx, iby, ibz, n0, n1);
+    p.as = node_index(sx, sy, sz, n1, n2);
+    p.bs = node_index(tx, ty, tz, n1, n2);
+    const double rs = P.rwnode[p.as], rt = P.rwnode[p.bs];
     const double qa = P.qfac * fabs(alpha);
-    const double ra = (double)wa.r, rb = (double)wb.r;
+    const double ra = (double)wa.x, rb = (double)wb.x;
     p.q = (qa * ra) * rb;
-    p.ka = (qa * (double)wa.s) * rb;
-    p.kb = (qa * ra) * (double)wb.s;
-    p.kas = p.q * ((T.rw[sx] * T.rw[n0 + sy]) * T.rw[n0 + n1 + sz]);
-    p.kbs = p.q * ((T.rw[tx] * T.rw[n0 + ty]) * T.rw[n0 + n1 + tz]);
+    p.ka = (qa * (double)wa.y) * rb;
+    p.kb = (qa * ra) * (double)wb.y;
+    p.kas = p.q * rs;
+    p.kbs = p.q * rt;
   } else {
     p.as = -1;
     p.bs = -1;
@@ -279,16 +285,16 @@ __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const Ta
   const bool in_a = (ax >= 0) & (ay >= 0) & (az >= 0), in_b = (bx >= 0) & (by >= 0) & (bz >= 0);
   const bool kept = in_a & in_b & (sx >= 0) & (sy >= 0) & (sz >= 0) & (tx >= 0) & (ty >= 0) & (tz >= 0);
   Pair p;
-  p.a = in_a ? (ax * n1 + ay) * n2 + az : -1;
-  p.b = in_b ? (bx * n1 + by) * n2 + bz : -1;
+  p.a = in_a ? node_index(ax, ay, az, n1, n2) : -1;
+  p.b = in_b ? node_index(bx, by, bz, n1, n2) : -1;
   if (kept) {
-    p.as = (sx * n1 + sy) * n2 + sz;
-    p.bs = (tx * n1 + ty) * n2 + tz;
+    p.as = node_index(sx, sy, sz, n1, n2);
+    p.bs = node_index(tx, ty, tz, n1, n2);
     p.q = P.qfac * fabs(alpha);
-    p.ka = p.q * ((T.rw[ax] * T.rw[n0 + ay]) * T.rw[n0 + n1 + az]);
-    p.kb = p.q * ((T.rw[bx] * T.rw[n0 + by]) * T.rw[n0 + n1 + bz]);
-    p.kas = p.q * ((T.rw[sx] * T.rw[n0 + sy]) * T.rw[n0 + n1 + sz]);
-    p.kbs = p.q * ((T.rw[tx] * T.rw[n0 + ty]) * T.rw[n0 + n1 + tz]);
+    p.ka = p.q * P.rwnode[p.a];
+    p.kb = p.q * P.rwnode[p.b];
+    p.kas = p.q * P.rwnode[p.as];
+    p.kbs = p.q * P.rwnode[p.bs];
   } else {
     p.as = -1;
     p.bs = -1;

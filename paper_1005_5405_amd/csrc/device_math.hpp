@@ -21,6 +21,11 @@ constexpr double kPiOver4 = 0.78539816339744830961566084581988;
 // ---------------------------------------------------------------- Philox --
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
 // 32x32->64 products; the key advances by the Weyl constants between rounds.
+// The three-operand exclusive ors are one v_bitop3 each (the first round,
+// whose counter words are mostly uniform, is left to the scalar unit).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 struct u32x4 {
   uint32_t x, y, z, w;
 };
@@ -35,9 +40,9 @@ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, uint32_t k1
     const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c.x;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c.z;
     u32x4 n;
-    n.x = (uint32_t)(p1 >> 32) ^ c.y ^ k0;
+    n.x = r == 0 ? (uint32_t)(p1 >> 32) ^ c.y ^ k0 : xor3((uint32_t)(p1 >> 32), c.y, k0);
     n.y = (uint32_t)p1;
-    n.z = (uint32_t)(p0 >> 32) ^ c.w ^ k1;
+    n.z = r == 0 ? (uint32_t)(p0 >> 32) ^ c.w ^ k1 : xor3((uint32_t)(p0 >> 32), c.w, k1);
     n.w = (uint32_t)p0;
     c = n;
   }
@@ -80,9 +85,13 @@ __device__ __forceinline__ void cos_sin_2pi(double u, double& cs, double& sn) {
 // ------------------------------------------------------------ node law --
 // A node index comes from a 12-bit field f of a Philox word: the Maxwellian
 // law is a direct inverse-CDF table icdf[f] = #{i >= 1 : T_i <= f}; the
-// uniform law is floor(f n / 2^12) (a 24-bit product).
+// uniform law is floor(f n / 2^12) (a 24-bit product, which runs at full rate
+// where the 32-bit one takes four issue slots; node indices likewise).
+__device__ __forceinline__ int node_index(int ix, int iy, int iz, int n1, int n2) {
+  return (int)(__umul24(__umul24((uint32_t)ix, (uint32_t)n1) + (uint32_t)iy, (uint32_t)n2) + (uint32_t)iz);
+}
 __device__ __forceinline__ int uniform_draw(uint32_t f, int n) {
-  return (int)((f * (uint32_t)n) >> kFieldBits);
+  return (int)(__umul24(f, (uint32_t)n) >> kFieldBits);
 }
 
 // ------------------------------------------------------------ streaming --

@@ -41,9 +41,11 @@ struct Params {
   double a[3], inv_cell[3];
   const double* vtab;     // [3][kMaxAxis] node velocities
   const double* omtab;    // [3][kMaxAxis] per-axis weights omega
-  const double* rwtab;    // [3][kMaxAxis] 1 / omega
-  const float4* nqtab;    // [3][kMaxAxis] {omega, p_phi, p_unif, 0} in FP32: weight
-                          // and realised Maxwellian / uniform laws of one axis
+  const double* rwnode;   // [nv] 1 / w of every node (product of the axes' 1 / omega)
+  const float2* nwtab;    // [nv] {w / p~, 1 / p~} of every node, FP32: w the midpoint
+                          // weight of Phi0, p~ = (1 - beta) p_phi + beta p_unif the
+                          // probability of drawing it from the mixture law
+  const double2* sctab;   // [8192] {sin, cos} polynomials of cos_sin_2pi over one octant
   const uint8_t* icdf;    // [3][kFieldSize] Maxwellian inverse CDF on 12-bit fields
   const float* cour;      // [2][kMaxAxis] Courant number |v| dt / d{x,y}
   const float* cour2;     // [2][kMaxAxis] C (1 - C) / 2
