@@ -82,13 +82,13 @@ __device__ __forceinline__ void gain_loss_adj(const Params& P, const TablesLDS& 
     const float4* rk = tcoef + (int64_t)group * nt;
     // one pass: PU records per thread; in the masked (last) pass slots past
     // the end of the table load and add nothing
-    auto pass = [&](uint32_t m0, const bool masked) {
+    auto pass = [&](uint32_t m0, uint32_t stride, const bool masked) {
       uint2 id[PU];
       float4 kk[PU];
       bool ok[PU];
 #pragma unroll
       for (int u = 0; u < PU; ++u) {
-        const uint32_t m = m0 + u * BLOCK;
+        const uint32_t m = m0 + u * stride;
         ok[u] = !masked || m < nt;
         id[u] = ok[u] ? ri[m] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[m] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -114,9 +114,7 @@ __device__ __forceinline__ void gain_loss_adj(const Params& P, const TablesLDS& 
               fma(eps, (double)ha[u], 1.0));
       }
     };
-    uint32_t m0 = tid;
-    for (; m0 + (PU - 1) * BLOCK < nt; m0 += PU * BLOCK) pass(m0, false);
-    if (m0 < nt) pass(m0, true);
+    table_walk<BLOCK, PU>(nt, tid, false, pass);
   } else {
     for (uint32_t m = tid; m < nt; m += BLOCK) {
       const Pair p = sample_pair(P, T, group, step, m, nullptr);
@@ -355,7 +353,7 @@ __global__ __launch_bounds__(BLOCK, 4) void collide_adj_kernel(Params P, const f
     __syncthreads();
     // ---- forward: increments and h^c, and the sums z
     const uint32_t group = (P.sample_group == 0) ? 0u : (uint32_t)(cell / P.sample_group);
-    gain_loss<BLOCK, TABLE, ACC_FIXED>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
+    gain_loss<BLOCK, TABLE, ACC_FIXED, 4, 0, false>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
     __syncthreads();
     double zs[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     auto hc_group = [&](int i, const double (&l)[V]) {

@@ -54,6 +54,7 @@ struct boltz_ctx {
   size_t collide_lds[2] = {0, 0};
   int64_t collide_grid[2] = {0, 0};
   int64_t ngroups = 0;          // sample groups (shared-sample mode)
+  int records = kRecordsPlain;  // what becomes of the drawn records
   // wall state the ratio tables Phi_w / Phi0 were last built for
   WallArgs ratio_walls{};
   std::vector<double> ratio_taub;   // bottom-face temperatures of that state
@@ -205,6 +206,26 @@ bool pick_part(const int (&n)[3], int ns, bool sampler, int& lo, int& nin) {
     }
   }
   return false;
+}
+
+// What becomes of the shared records between the sampler and the collision
+// (a table of nt records for each of ngroups sample groups):
+//   grouped by first node (group_kernel, 8 us, less where the y faces hide it)
+//   where the pair loops it shortens are long: 64x64 cells, 20^3, 20 000 pairs
+//   (8e7 record-cells) save 12 us a collision, so from 6e7 record-cells on,
+//   and 512 cells a group;
+//   else dealt to lanes (about 4 us of the sampler's latency for 4% of the
+//   pair loop): from 3e7 record-cells and 128 cells a group;
+//   else left in order (33x21 cells, 13x11x9 nodes, 3001 pairs, four cells a
+//   group: sampler launch 34 us dealt, 18 us in order).
+int record_mode(int mode, int64_t ngroups, int64_t ncells, int64_t nt, int nv) {
+  if (ngroups < 1 || (mode != ACC_FIXED && mode != ACC_PART && mode != ACC_HYBRID && mode != ACC_CAS))
+    return kRecordsPlain;
+  const double work = (double)ncells * (double)nt;
+  if ((mode == ACC_FIXED || mode == ACC_PART) && nv <= kGroupMaxNodes && nt >= kGroupBlock / 2 && work >= 6.0e7 &&
+      ncells / ngroups >= 512)
+    return kRecordsGroup;
+  return work >= 3.0e7 && ncells / ngroups >= 128 ? kRecordsDeal : kRecordsPlain;
 }
 
 // Accumulation mode and block sizes of the collide kernel: 64-bit
@@ -592,7 +613,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
         const double w = (c->om[0][ix] * c->om[1][iy]) * c->om[2][iz];
         const double psi[5] = {1.0, vx, vy, vz, (vx * vx + vy * vy) + vz * vz};
         int t = 0;
-        for (int k = 0; k < 5; ++k)
+        for (int k = 0; k < 6; ++k)
           for (int l = k; l < 5; ++l) m0[t++] += w * psi[k] * psi[l];
       }
   for (int k = 0; k < 2; ++k) {
@@ -758,6 +779,8 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   P.hyb_n = hn[1];
   P.hyb_ovf = hyb_rows ? reinterpret_cast<float*>(base + o_hyb) : nullptr;
   c->ngroups = ngroups;
+  c->records = seq ? kRecordsPlain : record_mode(cmode, ngroups, c->ncells, p->n_pairs, c->nv);
+  P.grouped = c->records == kRecordsGroup ? 1 : 0;
   c->tidx = ngroups ? reinterpret_cast<uint2*>(base + o_tidx) : nullptr;
   c->tcoef = ngroups ? reinterpret_cast<float4*>(base + o_tcoef) : nullptr;
   c->sidx = nsort ? reinterpret_cast<uint2*>(base + o_sidx) : c->tidx;
@@ -785,6 +808,15 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
     else (void)hipGetLastError();
   }
   hipError_t ea = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
+  if (ea == hipSuccess && P.grouped) {
+    ea = hipFuncSetAttribute((const void*)group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kGroupMaxNodes);
+    if (ea == hipSuccess)
+      ea = hipFuncSetAttribute((const void*)group_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               4 * kGroupMaxNodes);
+    if (ea == hipSuccess)
+      ea = hipFuncSetAttribute((const void*)wall_group_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               4 * kGroupMaxNodes);
+  }
   for (int t = 0; t < 2 && ea == hipSuccess && !seq; ++t) {
     const void* fn = collide_fn(cblock[t], t == 1, cmode, (p->flags & BOLTZ_CONTINUOUS_PAIRS) != 0);
     c->collide_lds[t] = cmode == ACC_HYBRID ? CollideLDS::hyb_bytes(c->nv, hn[t], nsum, t == 0)
@@ -911,10 +943,24 @@ static bool samples_with_walls(const boltz_ctx* c) {
   return c->ngroups > 0 && c->p.n_pairs > 0 && c->collide_mode != ACC_SPLIT;
 }
 
+// The drawn records rearranged by first node, where the problem asks for it.
+static void launch_group(const boltz_ctx* c, uint2* tidx, float4* tcoef, hipStream_t st) {
+  const dim3 grid((unsigned)((c->p.n_pairs + kGroupBlock - 1) / kGroupBlock), (unsigned)c->ngroups);
+  hipLaunchKernelGGL(group_kernel, grid, dim3(kGroupThreads), (size_t)c->nv * 4, st, tidx, tcoef,
+                     (int64_t)c->p.n_pairs, c->nv);
+}
+
+// The adjoint's two pair loops take their records dealt to lanes, not grouped
+// (64x64 cavity, 20^3, 20 000 pairs: reverse step 834 us dealt, 888 with a
+// grouped form of both loops, which spills).
+static int adjoint_records(const boltz_ctx* c) {
+  return c->records == kRecordsGroup ? kRecordsDeal : c->records;
+}
+
 // The face densities; with sample_step >= 0 (and samples_with_walls) the
 // records of that step are drawn in the last face launch.
 static int launch_walls(boltz_ctx* c, const float* h, const WallArgs& W, const boltz_walls* walls,
-                        hipStream_t st, int64_t sample_step = -1) {
+                        hipStream_t st, int64_t sample_step = -1, int records = kRecordsPlain) {
   const int rc = ensure_ratio(c, W, walls, st);
   if (rc != BOLTZ_OK) return rc;
   auto launch = [&](auto kern, int nface) {
@@ -922,26 +968,35 @@ static int launch_walls(boltz_ctx* c, const float* h, const WallArgs& W, const b
     hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(kWallBlock), 0, st, c->P, h, nface, per_xcd);
   };
   // order 2: x faces first, then the y faces, which read the x-face
-  // densities for their x-swept rows; the pair records go with the last
-  // (and, for order 2, longer) launch
+  // densities for their x-swept rows.  The pair records go with the last
+  // (and, for order 2, longer) launch; records to be grouped with the first,
+  // their grouping with the last
   const bool with_samples = sample_step >= 0 && samples_with_walls(c);
-  auto launch_last = [&](auto kern, auto kern_s, int nface) {
-    if (!with_samples) {
-      launch(kern, nface);
-      return;
-    }
+  const bool group = with_samples && records == kRecordsGroup;
+  auto launch_drawing = [&](auto kern, int nface) {
     const int per_xcd = (nface + 7) / 8;
     const int nb = (int)((c->p.n_pairs + kSampleBlock - 1) / kSampleBlock);
     const int nsum = c->n[0] + c->n[1] + c->n[2];
-    hipLaunchKernelGGL(kern_s, dim3((unsigned)(8 * per_xcd + nb * c->ngroups)), dim3(kWallBlock),
+    hipLaunchKernelGGL(kern, dim3((unsigned)(8 * per_xcd + nb * c->ngroups)), dim3(kWallBlock),
                        TablesLDS::bytes(nsum, true), st, c->P, h, nface, per_xcd, nb, (uint32_t)sample_step,
-                       c->tidx, c->tcoef, c->seq ? 0 : 1);
+                       c->tidx, c->tcoef, records);
   };
   if (c->p.order == 2) {
-    launch(wall_kernel<0>, 2 * c->p.ny);
-    launch_last(wall_kernel<1>, wall_sample_kernel<1>, 2 * c->p.nx);
+    if (group) {
+      launch_drawing(wall_sample_kernel<0>, 2 * c->p.ny);
+      const int per_xcd = (2 * c->p.nx + 7) / 8, nb = (int)((c->p.n_pairs + kGroupBlock - 1) / kGroupBlock);
+      hipLaunchKernelGGL(wall_group_kernel, dim3((unsigned)(8 * per_xcd + nb * c->ngroups)), dim3(kWallBlock),
+                         (size_t)c->nv * 4, st, c->P, h, 2 * c->p.nx, per_xcd, nb, c->tidx, c->tcoef);
+    } else {
+      launch(wall_kernel<0>, 2 * c->p.ny);
+      if (with_samples) launch_drawing(wall_sample_kernel<1>, 2 * c->p.nx);
+      else launch(wall_kernel<1>, 2 * c->p.nx);
+    }
+  } else if (with_samples) {
+    launch_drawing(wall_sample_kernel<0>, 2 * (c->p.nx + c->p.ny));
+    if (group) launch_group(c, c->tidx, c->tcoef, st);
   } else {
-    launch_last(wall_kernel<0>, wall_sample_kernel<0>, 2 * (c->p.nx + c->p.ny));
+    launch(wall_kernel<0>, 2 * (c->p.nx + c->p.ny));
   }
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "wall_kernel launch");
@@ -1029,28 +1084,26 @@ static void launch_collide_b(boltz_ctx* c, bool table, const float* hs, float* h
 
 // Shared-sample mode: the pair records of every group for this step
 // (ACC_SPLIT: then sorted by the velocity half of their targets).
-static void launch_samples(boltz_ctx* c, uint32_t s32, hipStream_t st, const RecordTables& R) {
+static void launch_samples(boltz_ctx* c, uint32_t s32, hipStream_t st, const RecordTables& R, int records) {
   if (c->ngroups > 0 && c->p.n_pairs > 0) {
     const int nsum = c->n[0] + c->n[1] + c->n[2];
     const dim3 grid((unsigned)((c->p.n_pairs + kSampleBlock - 1) / kSampleBlock), (unsigned)c->ngroups);
-    // records in sample order for the sequential collision, else dealt to
-    // lanes where no sort follows
     hipLaunchKernelGGL(sample_kernel, grid, dim3(kSampleBlock), TablesLDS::bytes(nsum, true), st, c->P, s32, R.sidx,
-                       R.scoef, (R.sidx == R.tidx && !c->seq) ? 1 : 0);
+                       R.scoef, records);
+    if (records == kRecordsGroup) launch_group(c, R.tidx, R.tcoef, st);
     if (R.sidx != R.tidx)
       hipLaunchKernelGGL(split_sort_kernel, dim3((unsigned)c->ngroups), dim3(kSortBlock), 0, st, R.sidx, R.scoef,
                          R.tidx, R.tcoef, (int64_t)c->p.n_pairs, (unsigned)CollideLDS::half(c->nv));
   }
 }
 
-static void launch_samples(boltz_ctx* c, uint32_t s32, hipStream_t st) { launch_samples(c, s32, st, own_tables(c)); }
 
 // The collision with the records in R (drawn: already written this step).
 static int launch_collide_r(boltz_ctx* c, const float* hs, float* hout, int64_t step, uint32_t flags,
                             double* defect, hipStream_t st, bool drawn, const RecordTables& R) {
   const uint32_t s32 = (uint32_t)step;
   const bool table = c->ngroups > 0;
-  if (!drawn) launch_samples(c, s32, st, R);
+  if (!drawn) launch_samples(c, s32, st, R, c->records);
   if (c->seq) {
     // Alg. 3: the record levels of every sample group, then one wavefront
     // per cell
@@ -1111,7 +1164,7 @@ static int stream_step(boltz_ctx* c, const float* h_in, float* h_out, const bolt
   const bool cavity = c->p.bc == BOLTZ_BC_CAVITY;
   if (cavity && !walls_ok(walls, c->p.nx)) return fail(c, BOLTZ_EINVAL, "boltz_stream: cavity needs valid walls");
   int rc = BOLTZ_OK;
-  if (cavity) rc = launch_walls(c, h_in, make_walls(walls), walls, st, sample_step);
+  if (cavity) rc = launch_walls(c, h_in, make_walls(walls), walls, st, sample_step, c->records);
   if (drawn) *drawn = cavity && sample_step >= 0 && samples_with_walls(c);
   if (rc == BOLTZ_OK) rc = launch_stream(c, h_in, h_out, st);
   return rc;
@@ -1248,7 +1301,9 @@ static void launch_collide_adj_b(boltz_ctx* c, bool table, const float* hs, cons
                                  uint32_t s32, uint32_t flags, hipStream_t st) {
   const int t = table ? 1 : 0;
   auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, c->P, hs, lo, ls, s32,
+    Params P = c->P;
+    P.grouped = 0;
+    hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, P, hs, lo, ls, s32,
                        flags, c->tidx, c->tcoef);
   };
   // four nodes per access: whole quadruples per row, 16-byte aligned buffers
@@ -1265,7 +1320,7 @@ static int launch_collide_adj(boltz_ctx* c, const float* hs, const double* lo, d
                               uint32_t flags, hipStream_t st, bool drawn = false) {
   const uint32_t s32 = (uint32_t)step;
   const bool table = c->ngroups > 0;
-  if (!drawn) launch_samples(c, s32, st);
+  if (!drawn) launch_samples(c, s32, st, own_tables(c), adjoint_records(c));
   const int block = c->adj_block[table ? 1 : 0];
   if (block == 256) launch_collide_adj_b<256>(c, table, hs, lo, ls, s32, flags, st);
   else if (block == 512) launch_collide_adj_b<512>(c, table, hs, lo, ls, s32, flags, st);
@@ -1327,7 +1382,7 @@ int boltz_step_adjoint(boltz_ctx* c, const float* h_in, const double* lam_out, d
   // forward streaming again (also leaves the face densities of h_in in P.nw),
   // the step's pair records drawn in its face launch as in boltz_step
   int rc = BOLTZ_OK;
-  if (cavity) rc = launch_walls(c, h_in, W, walls, st, step);
+  if (cavity) rc = launch_walls(c, h_in, W, walls, st, step, adjoint_records(c));
   const bool drawn = cavity && step >= 0 && samples_with_walls(c);
   if (rc == BOLTZ_OK) rc = launch_stream(c, h_in, c->adj_hs, st);
   if (rc != BOLTZ_OK) return rc;
@@ -1448,9 +1503,11 @@ struct boltz_batch {
   size_t dbytes = 0;
   BatchCav* cavs = nullptr;
   // first unit of each problem in the batched launches: x faces (all faces
-  // for order 1), y faces, stream units, sample blocks, sort workgroups
-  int* start[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
-  int total[5] = {0, 0, 0, 0, 0};
+  // for order 1), y faces, stream units, sample blocks, sort workgroups,
+  // blocks of grouped records
+  int* start[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  int total[6] = {0, 0, 0, 0, 0, 0};
+  size_t group_lds = 0;
   int2* items = nullptr;
   int nitems = 0;
   std::vector<BatchClass> cls;
@@ -1543,8 +1600,8 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
   }
   // ---- descriptors, launch ranges, work items
   std::vector<BatchCav> cavs(count);
-  std::vector<int> st[5], stb(count + 1, 0);
-  for (int k = 0; k < 5; ++k) st[k].assign(count + 1, 0);
+  std::vector<int> st[6], stb(count + 1, 0);
+  for (int k = 0; k < 6; ++k) st[k].assign(count + 1, 0);
   std::vector<double> cost(count);
   std::vector<int> cls_of(count);
   int64_t off = 0;
@@ -1566,6 +1623,7 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
     C.sidx = part ? c->tidx : c->sidx;
     C.scoef = part ? c->tcoef : c->scoef;
     C.mode = part ? ACC_PART : c->batch_mode;
+    C.records = C.sidx == C.tidx ? c->records : kRecordsPlain;
     b->hoff.push_back(off);
     off += c->ncells * (int64_t)c->nv;
     const bool cavity = c->p.bc == BOLTZ_BC_CAVITY;
@@ -1583,9 +1641,11 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
     const int64_t sblocks =
         (c->ngroups > 0 && c->p.n_pairs > 0) ? c->ngroups * ((c->p.n_pairs + kSampleBlock - 1) / kSampleBlock) : 0;
     const int64_t sorts = (!part && c->sidx != c->tidx) ? c->ngroups : 0;
-    const int64_t nxt[5] = {(int64_t)st[0][i] + nf0, (int64_t)st[1][i] + nf1, (int64_t)st[2][i] + units,
-                            (int64_t)st[3][i] + sblocks, (int64_t)st[4][i] + sorts};
-    for (int k = 0; k < 5; ++k) {
+    const int64_t gblocks = c->P.grouped ? c->ngroups * ((c->p.n_pairs + kGroupBlock - 1) / kGroupBlock) : 0;
+    if (gblocks) b->group_lds = std::max(b->group_lds, (size_t)c->nv * 4);
+    const int64_t nxt[6] = {(int64_t)st[0][i] + nf0,     (int64_t)st[1][i] + nf1,   (int64_t)st[2][i] + units,
+                            (int64_t)st[3][i] + sblocks, (int64_t)st[4][i] + sorts, (int64_t)st[5][i] + gblocks};
+    for (int k = 0; k < 6; ++k) {
       if (nxt[k] >= ((int64_t)1 << 31) / 8) {
         boltz_batch_destroy(b);
         return bfail(nullptr, BOLTZ_EINVAL, "boltz_batch_create: batch too large for one launch per phase");
@@ -1619,7 +1679,7 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
     b->pair_cells += c->ncells * c->p.n_pairs;
   }
   b->nodes = off;
-  for (int k = 0; k < 5; ++k) b->total[k] = st[k][count];
+  for (int k = 0; k < 6; ++k) b->total[k] = st[k][count];
   b->total_b = stb[count];
   // work items grouped by class, by decreasing cost within a class
   std::vector<int2> items;
@@ -1637,8 +1697,8 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
   // ---- one device allocation
   size_t o = 0;
   const size_t o_cavs = o; o = align256(o + sizeof(BatchCav) * count);
-  size_t o_st[5];
-  for (int k = 0; k < 5; ++k) { o_st[k] = o; o = align256(o + sizeof(int) * (count + 1)); }
+  size_t o_st[6];
+  for (int k = 0; k < 6; ++k) { o_st[k] = o; o = align256(o + sizeof(int) * (count + 1)); }
   const size_t o_stb = o; o = align256(o + sizeof(int) * (count + 1));
   const size_t o_items = o; o = align256(o + sizeof(int2) * items.size());
   const size_t o_step = o; o = align256(o + 4);
@@ -1650,12 +1710,12 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
   b->dbytes = o;
   unsigned char* base = static_cast<unsigned char*>(b->dmem);
   b->cavs = reinterpret_cast<BatchCav*>(base + o_cavs);
-  for (int k = 0; k < 5; ++k) b->start[k] = reinterpret_cast<int*>(base + o_st[k]);
+  for (int k = 0; k < 6; ++k) b->start[k] = reinterpret_cast<int*>(base + o_st[k]);
   b->start_b = reinterpret_cast<int*>(base + o_stb);
   b->items = reinterpret_cast<int2*>(base + o_items);
   b->step_dev = reinterpret_cast<uint32_t*>(base + o_step);
   e = hipMemcpy(b->cavs, cavs.data(), sizeof(BatchCav) * count, hipMemcpyHostToDevice);
-  for (int k = 0; k < 5 && e == hipSuccess; ++k)
+  for (int k = 0; k < 6 && e == hipSuccess; ++k)
     e = hipMemcpy(b->start[k], st[k].data(), sizeof(int) * (count + 1), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->start_b, stb.data(), sizeof(int) * (count + 1), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(b->items, items.data(), sizeof(int2) * items.size(), hipMemcpyHostToDevice);
@@ -1786,6 +1846,9 @@ int boltz_batch_step(boltz_batch* b, const float* h_in, float* h_out, const bolt
   if (b->total[3] > 0)
     hipLaunchKernelGGL(sample_batch_kernel, dim3(b->total[3]), dim3(kSampleBlock), b->sample_lds, st, b->cavs,
                        b->start[3], b->count, b->step_dev);
+  if (b->total[5] > 0)
+    hipLaunchKernelGGL(group_batch_kernel, dim3(b->total[5]), dim3(kGroupThreads), b->group_lds, st, b->cavs,
+                       b->start[5], b->count);
   if (b->total[4] > 0)
     hipLaunchKernelGGL(split_sort_batch_kernel, dim3(b->total[4]), dim3(kSortBlock), 0, st, b->cavs, b->start[4],
                        b->count);

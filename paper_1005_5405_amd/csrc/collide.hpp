@@ -343,9 +343,21 @@ __global__ __launch_bounds__(256) void debug_pairs_kernel(Params P, int64_t cell
 // once per step into two arrays, idx = {a | b << 16, a* | b* << 16} and
 // coef = {q/w_a*, q/w_b*, q/w_a, q/w_b} in FP32; a discarded pair is stored
 // with a* = a, b* = b and zero coefficients.
+// Where the records are grouped by their first node (kGroupFlag below), a is
+// the likelier node of the two (the smaller 1 / w): the sample is symmetric in
+// them.  The sequential collision keeps the order drawn.
 __device__ __forceinline__ void sample_pair_record(const Params& P, const TablesLDS& T, uint32_t step,
-                                                   uint32_t group, int64_t i, uint2& id, float4& coef) {
-  const Pair p = sample_pair(P, T, group, step, (uint32_t)i, nullptr);
+                                                   uint32_t group, int64_t i, bool likelier, uint2& id,
+                                                   float4& coef) {
+  Pair p = sample_pair(P, T, group, step, (uint32_t)i, nullptr);
+  if (likelier && p.as >= 0 && P.rwnode[p.b] < P.rwnode[p.a]) {
+    const int t = p.a;
+    p.a = p.b;
+    p.b = t;
+    const double k = p.ka;
+    p.ka = p.kb;
+    p.kb = k;
+  }
   // a discarded continuous pair may have no cell for v or v1: node 0 then
   // (its coefficients are zero)
   const uint32_t a = p.a < 0 ? 0u : (uint32_t)p.a, b = p.b < 0 ? 0u : (uint32_t)p.b;
@@ -365,6 +377,10 @@ __device__ __forceinline__ void sample_pair_record(const Params& P, const Tables
 // block call this (valid: the thread holds a record; n_blk: the block's
 // record count; deal: permute, else store in place).  sh: 1280 words of LDS.
 constexpr int kSampleBlock = 1024;
+
+// What becomes of the records as they are drawn: stored in order, dealt to
+// lanes, or stored in order for group_kernel.
+enum : int { kRecordsPlain = 0, kRecordsDeal = 1, kRecordsGroup = 2 };
 
 __device__ __forceinline__ void store_records(uint2 id, float4 coef, bool valid, int n_blk, bool deal,
                                               uint2* __restrict__ tidx, float4* __restrict__ tcoef,
@@ -437,20 +453,19 @@ __device__ __forceinline__ void store_records(uint2 id, float4 coef, bool valid,
 // One block of kSampleBlock records of a sample group, from record base:
 // drawn (one per thread), then stored through store_records.
 __device__ __forceinline__ void sample_block(const Params& P, const TablesLDS& T, uint32_t step, uint32_t group,
-                                             int64_t base, bool deal, uint2* __restrict__ tidx,
+                                             int64_t base, int deal, uint2* __restrict__ tidx,
                                              float4* __restrict__ tcoef, unsigned* sh) {
   const int64_t nt = P.n_pairs;
   const int n_blk = (int)(nt - base < kSampleBlock ? nt - base : kSampleBlock);
   const bool valid = (int)threadIdx.x < n_blk;
   uint2 id = make_uint2(0u, 0u);
   float4 coef = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (valid) sample_pair_record(P, T, step, group, base + threadIdx.x, id, coef);
-  store_records(id, coef, valid, n_blk, deal, tidx + (int64_t)group * nt + base, tcoef + (int64_t)group * nt + base,
+  if (valid) sample_pair_record(P, T, step, group, base + threadIdx.x, deal == kRecordsGroup, id, coef);
+  store_records(id, coef, valid, n_blk, deal == kRecordsDeal, tidx + (int64_t)group * nt + base, tcoef + (int64_t)group * nt + base,
                 sh);
 }
 
-// Grid: (ceil(N_t / kSampleBlock), groups).  deal: no sort follows (the
-// records go straight to the collision), so they are dealt to lanes.
+// Grid: (ceil(N_t / kSampleBlock), groups).
 __global__ __launch_bounds__(kSampleBlock) void sample_kernel(Params P, uint32_t step, uint2* __restrict__ tidx,
                                                               float4* __restrict__ tcoef, int deal) {
   extern __shared__ __align__(16) unsigned char dsm[];
@@ -458,7 +473,142 @@ __global__ __launch_bounds__(kSampleBlock) void sample_kernel(Params P, uint32_t
   TablesLDS T;
   load_tables(P, dsm, true, T);
   __syncthreads();
-  sample_block(P, T, step, blockIdx.y, (int64_t)blockIdx.x * kSampleBlock, deal != 0, tidx, tcoef, sh);
+  sample_block(P, T, step, blockIdx.y, (int64_t)blockIdx.x * kSampleBlock, deal, tidx, tcoef, sh);
+}
+
+// ------------------------------------------------- records by first node --
+// The collision's pair loop is bound by its LDS operations, two gathers and
+// four 64-bit adds per record and cell.  Most records share their likelier
+// node with others (20^3 on [-5, 5], 8192 records: 86% in quadruples of one
+// node), so each block of kGroupBlock records is rearranged in place into
+// chunks of 256 records, record u of lane l at 64 u + l: first the chunks
+// whose 64 lanes hold four records of one first node each (marked by
+// kGroupFlag in every record's a), then the rest.  A marked lane gathers h^s
+// at a once and adds the sum of its four losses at a once (an exact integer
+// sum): 13 adds and 5 gathers in place of 16 and 8.  The order within a block
+// is that of the LDS counters, which the fixed-point sums do not depend on.
+// One workgroup per block; dynamic LDS: one counter per node.
+// One collision launch, dealt to lanes -> grouped: 64x64 cells, 20^3, 20 000
+// pairs 280 -> 268 us; 200x200, 24^3, 50 000 pairs 5.59 -> 5.28 ms.  The adds
+// and gathers that fall away are those that the dealing had made free of
+// bank conflicts.  This kernel: 8 us for 20 000 records.
+constexpr int kGroupRecords = 4;                      // per thread
+constexpr int kGroupThreads = 1024;
+constexpr int kGroupBlock = kGroupRecords * kGroupThreads;
+constexpr int kGroupMaxNodes = 16384;
+constexpr unsigned kGroupFlag = 0x8000u;              // in a record's a (velocity nodes < 2^15)
+constexpr unsigned kNodeMask = 0x7FFFu;
+
+// n: the records from tidx, tcoef on (at most kGroupBlock).
+__device__ __forceinline__ void group_block(uint2* tidx, float4* tcoef, int n, int nv, unsigned* cnt,
+                                            unsigned* sh) {
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  // (plain vector types: arrays of float4 objects go to scratch memory)
+  typedef float f4v __attribute__((ext_vector_type(4)));
+  typedef unsigned u2v __attribute__((ext_vector_type(2)));
+  u2v* idx = reinterpret_cast<u2v*>(tidx);
+  f4v* coef = reinterpret_cast<f4v*>(tcoef);
+  u2v id[kGroupRecords];
+  f4v co[kGroupRecords];
+#pragma unroll
+  for (int r = 0; r < kGroupRecords; ++r) {
+    const int i = min(r * kGroupThreads + tid, n - 1);
+    id[r] = idx[i];
+    co[r] = coef[i];
+  }
+  for (int j = tid; j < nv; j += kGroupThreads) cnt[j] = 0u;
+  if (tid == 0) sh[17] = 0u;
+  __syncthreads();
+  unsigned rank[kGroupRecords];
+#pragma unroll
+  for (int r = 0; r < kGroupRecords; ++r) {
+    rank[r] = 0u;
+    if (r * kGroupThreads + tid < n) rank[r] = atomicAdd(&cnt[id[r].x & kNodeMask], 1u);
+  }
+  __syncthreads();
+  // first quadruple of every node, in the order of the threads that hold
+  // them (thread t: nodes t, t + 1024, ...); a counter becomes count |
+  // (first << 16)
+  unsigned sum = 0;
+  for (int j = tid; j < nv; j += kGroupThreads) sum += cnt[j] >> 2;
+  unsigned inc = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned a = __shfl_up(inc, d, 64);
+    if (lane >= d) inc += a;
+  }
+  if (lane == 63) sh[wid] = inc;
+  __syncthreads();
+  if (tid == 0) {
+    unsigned run = 0;
+    for (int w = 0; w < kGroupThreads / 64; ++w) {
+      const unsigned c = sh[w];
+      sh[w] = run;
+      run += c;
+    }
+    sh[16] = run;
+  }
+  __syncthreads();
+  unsigned first = sh[wid] + (inc - sum);
+  for (int j = tid; j < nv; j += kGroupThreads) {
+    const unsigned c = cnt[j];
+    cnt[j] = c | (first << 16);
+    first += c >> 2;
+  }
+  const unsigned chunks = sh[16] >> 6, full = chunks << 6;  // whole chunks and their quadruples
+  const float inv = chunks ? __frcp_rn((float)chunks) : 0.0f;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kGroupRecords; ++r) {
+    const bool in = r * kGroupThreads + tid < n;
+    const unsigned c = cnt[id[r].x & kNodeMask], quad = (c >> 16) + (rank[r] >> 2);
+    const bool grouped = in && rank[r] < (c & 0xFFFCu) && quad < full;
+    const bool rest = in && !grouped;
+    // positions of the rest: one counter step per wavefront
+    const unsigned long long m = __ballot(rest);
+    unsigned base = 0;
+    if (lane == 0 && m) base = atomicAdd(&sh[17], (unsigned)__popcll(m));
+    base = __builtin_amdgcn_readfirstlane(base);
+    // consecutive quadruples (of one node) go to different chunks: the lanes
+    // of a wavefront then add at different nodes
+    unsigned l = (unsigned)((float)quad * inv);
+    if (l * chunks > quad) --l;
+    else if ((l + 1u) * chunks <= quad) ++l;
+    const unsigned pos = grouped ? (quad - l * chunks) * 256u + (rank[r] & 3u) * 64u + l
+                                 : 4u * full + base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+    if (in) {
+      if (grouped) id[r].x |= kGroupFlag;
+      idx[pos] = id[r];
+      coef[pos] = co[r];
+    }
+  }
+}
+
+// Grid: (ceil(N_t / kGroupBlock), groups), in place.
+__global__ __launch_bounds__(kGroupThreads) void group_kernel(uint2* tidx, float4* tcoef, int64_t nt, int nv) {
+  extern __shared__ __align__(16) unsigned char dsm[];
+  __shared__ unsigned sh[18];
+  const int64_t base = (int64_t)blockIdx.y * nt + (int64_t)blockIdx.x * kGroupBlock;
+  const int64_t left = nt - (int64_t)blockIdx.x * kGroupBlock;
+  group_block(tidx + base, tcoef + base, (int)(left < kGroupBlock ? left : kGroupBlock), nv,
+              reinterpret_cast<unsigned*>(dsm), sh);
+}
+
+// The same for the grouped problems of a batch: start[c] = first block of
+// problem c.
+__global__ __launch_bounds__(kGroupThreads) void group_batch_kernel(const BatchCav* __restrict__ cavs,
+                                                                    const int* __restrict__ start, int count) {
+  extern __shared__ __align__(16) unsigned char dsm[];
+  __shared__ unsigned sh[18];
+  const int u = blockIdx.x;
+  if (u >= start[count]) return;
+  const int c = find_cav(start, count, u);
+  const BatchCav& C = cavs[c];
+  const int64_t nt = C.P.n_pairs;
+  const int nb = (int)((nt + kGroupBlock - 1) / kGroupBlock), local = u - start[c];
+  const int64_t g = local / nb, at = (int64_t)(local - (int)g * nb) * kGroupBlock, left = nt - at;
+  group_block(C.tidx + g * nt + at, C.tcoef + g * nt + at, (int)(left < kGroupBlock ? left : kGroupBlock), C.P.nv,
+              reinterpret_cast<unsigned*>(dsm), sh);
 }
 
 // Pattern of a shared-sample record for the split accumulation: bit k is
@@ -529,7 +679,7 @@ __global__ __launch_bounds__(kSampleBlock) void sample_batch_kernel(const BatchC
   TablesLDS T;
   load_tables(P, dsm, true, T);
   __syncthreads();
-  sample_block(P, T, *step_dev, group, (int64_t)(local - (int)group * nb) * kSampleBlock, C.sidx == C.tidx, C.sidx,
+  sample_block(P, T, *step_dev, group, (int64_t)(local - (int)group * nb) * kSampleBlock, C.records, C.sidx,
                C.scoef, sh);
 }
 
@@ -855,6 +1005,15 @@ __device__ __forceinline__ void scatter(float* accf, unsigned long long* acc64, 
   }
 }
 
+// Whether four 64-bit values are all in the fixed-point window.
+__device__ __forceinline__ bool in_window4(long long d0, long long d1, long long d2, long long d3) {
+  return in_fixed_window(d0) & in_fixed_window(d1) & in_fixed_window(d2) & in_fixed_window(d3);
+}
+
+__device__ __forceinline__ void lds_add64(unsigned long long* p, long long d) {
+  __hip_atomic_fetch_add(p, (unsigned long long)d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // S3 + S4 for one cell (Eqs. monteCarloInt, collision_step in Jacobi form):
 // every sample reads the post-stream tile hs and adds its gain and loss to
 // the accumulators.  TABLE: the pairs are the records of sample_kernel for
@@ -862,7 +1021,29 @@ __device__ __forceinline__ void scatter(float* accf, unsigned long long* acc64, 
 // gathers are in flight together; else they are drawn here.
 // DRAW (pairs drawn here, not TABLE): 1 the node law, 2 continuous pairs,
 // 0 whichever the problem asks for (chosen once, outside the loop).
-template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0>
+// Walk of a table of nt records by BLOCK threads, PU per thread and pass:
+// pass(first record, distance, masked).  chunked: in chunks of 256 records per
+// wavefront, record u of a lane 64 u further (the order of group_kernel);
+// else all threads side by side, so that the last pass spreads over every
+// wavefront.  Either way record m goes to lane m mod 64.
+template <int BLOCK, int PU, class Pass>
+__device__ __forceinline__ void table_walk(uint32_t nt, int tid, bool chunked, Pass&& pass) {
+  uint32_t m = tid;
+  if (chunked) {
+    const uint32_t whole = nt & ~255u;
+    for (uint32_t c = (uint32_t)(tid >> 6) * 256u; c < whole; c += (BLOCK / 64) * 256u) {
+#pragma unroll
+      for (uint32_t h = 0; h < 256u; h += 64u * PU) pass(c + h + (uint32_t)(tid & 63), 64u, false);
+    }
+    m += whole;
+  } else {
+    for (; m + (PU - 1) * BLOCK < nt; m += PU * BLOCK) pass(m, BLOCK, false);
+  }
+  if (m < nt) pass(m, BLOCK, true);
+}
+
+// GROUP: the records may be grouped by first node (group_kernel).
+template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0, bool GROUP = MODE == ACC_FIXED>
 __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, const float* hs, float* accf,
                                           unsigned long long* acc64, uint32_t group, uint32_t step,
                                           const uint2* __restrict__ tidx, const float4* __restrict__ tcoef,
@@ -873,19 +1054,50 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
   if (TABLE) {
     const uint2* ri = tidx + (int64_t)group * nt;
     const float4* rk = tcoef + (int64_t)group * nt;
-    // one pass: PU records per thread, loads and gathers in flight together;
-    // in the masked (last) pass slots past the end of the table load and
-    // add nothing
-    auto pass = [&](uint32_t m, const bool masked) {
+    // one pass: PU records per thread (m, m + stride, ...), loads and gathers
+    // in flight together; in a masked pass slots past the end of the table
+    // load and add nothing
+    auto pass = [&](uint32_t m, uint32_t stride, const bool masked) {
       uint2 id[PU];
       float4 kk[PU];
       bool ok[PU];
 #pragma unroll
       for (int u = 0; u < PU; ++u) {
-        const uint32_t mu = m + u * BLOCK;
+        const uint32_t mu = m + u * stride;
         ok[u] = !masked || mu < nt;
         id[u] = ok[u] ? ri[mu] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[mu] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      if (GROUP && !masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
+        // the PU records of a lane share their first node: one gather and
+        // one add there
+        const int a = (int)(id[0].x & kNodeMask);
+        const float ha = hs[a];
+        float hb[PU];
+#pragma unroll
+        for (int u = 0; u < PU; ++u) hb[u] = hs[id[u].x >> 16];
+        long long da = 0;
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+          const double g = (double)((ha + hb[u]) + (epsf * ha) * hb[u]);
+          const int b = (int)(id[u].x >> 16), as = (int)(id[u].y & 0xFFFFu), bs = (int)(id[u].y >> 16);
+          const long long d0 = fixed_of(kk[u].x, g), d1 = fixed_of(kk[u].y, g), d2 = fixed_of(-kk[u].z, g),
+                          d3 = fixed_of(-kk[u].w, g);
+          if (__all(in_window4(d0, d1, d2, d3))) {
+            lds_add64(&acc64[as], d0);
+            lds_add64(&acc64[bs], d1);
+            lds_add64(&acc64[b], d3);
+            da += d2;
+          } else {
+            lds_add_fixed_or(acc64, accf, as, d0, kk[u].x, g);
+            lds_add_fixed_or(acc64, accf, bs, d1, kk[u].y, g);
+            lds_add_fixed_or(acc64, accf, b, d3, -kk[u].w, g);
+            if (in_fixed_window(d2)) da += d2;
+            else lds_add(&accf[a], (float)(-kk[u].z * g));
+          }
+        }
+        lds_add64(&acc64[a], da);
+        return;
       }
       float ha[PU], hb[PU];
 #pragma unroll
@@ -919,9 +1131,7 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
         }
       }
     };
-    uint32_t m = tid;
-    for (; m + (PU - 1) * BLOCK < nt; m += PU * BLOCK) pass(m, false);
-    if (m < nt) pass(m, true);
+    table_walk<BLOCK, PU>(nt, tid, GROUP && P.grouped, pass);
   } else {
     auto draw = [&](auto&& sampler) {
       for (uint32_t m = tid; m < nt; m += BLOCK) {
@@ -955,16 +1165,58 @@ __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS&
   if (TABLE) {
     const uint2* ri = tidx + (int64_t)group * nt;
     const float4* rk = tcoef + (int64_t)group * nt;
-    auto pass = [&](uint32_t m, const bool masked) {
+    auto pass = [&](uint32_t m, uint32_t stride, const bool masked) {
       uint2 id[PU];
       float4 kk[PU];
       bool ok[PU];
 #pragma unroll
       for (int u = 0; u < PU; ++u) {
-        const uint32_t mu = m + u * BLOCK;
+        const uint32_t mu = m + u * stride;
         ok[u] = !masked || mu < nt;
         id[u] = ok[u] ? ri[mu] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[mu] : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+      if (!masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
+        // the PU records of a lane share their first node
+        const int a = (int)(id[0].x & kNodeMask);
+        const bool ia = Q.inner(a);
+        float ha = Q.tile[ia ? a - Q.lo : 0], hb[PU];
+        bool ib[PU];
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+          const int b = (int)(id[u].x >> 16);
+          ib[u] = Q.inner(b);
+          hb[u] = Q.tile[ib[u] ? b - Q.lo : 0];
+        }
+        if (!ia) ha = Q.hg[a];
+#pragma unroll
+        for (int u = 0; u < PU; ++u)
+          if (!ib[u]) hb[u] = Q.hg[id[u].x >> 16];
+        long long da = 0;
+#pragma unroll
+        for (int u = 0; u < PU; ++u) {
+          const double g = (double)((ha + hb[u]) + (epsf * ha) * hb[u]);
+          const int b = (int)(id[u].x >> 16), as = (int)(id[u].y & 0xFFFFu), bs = (int)(id[u].y >> 16);
+          const long long d0 = fixed_of(kk[u].x, g), d1 = fixed_of(kk[u].y, g), d2 = fixed_of(-kk[u].z, g),
+                          d3 = fixed_of(-kk[u].w, g);
+          if (__all(in_window4(d0, d1, d2, d3))) {
+            lds_add64(&Q.acc[as], d0);
+            lds_add64(&Q.acc[bs], d1);
+            lds_add64(&Q.acc[b], d3);
+            da += d2;
+          } else {
+            if (in_fixed_window(d0)) lds_add64(&Q.acc[as], d0);
+            else part_wide(Q, as, kk[u].x, g);
+            if (in_fixed_window(d1)) lds_add64(&Q.acc[bs], d1);
+            else part_wide(Q, bs, kk[u].y, g);
+            if (in_fixed_window(d3)) lds_add64(&Q.acc[b], d3);
+            else part_wide(Q, b, -kk[u].w, g);
+            if (in_fixed_window(d2)) da += d2;
+            else part_wide(Q, a, -kk[u].z, g);
+          }
+        }
+        lds_add64(&Q.acc[a], da);
+        return;
       }
       float ha[PU], hb[PU];
       bool ia[PU], ib[PU];
@@ -989,9 +1241,7 @@ __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS&
                        (int)(id[u].y >> 16), kk[u].x, kk[u].y, kk[u].z, kk[u].w, g);
       }
     };
-    uint32_t m = tid;
-    for (; m + (PU - 1) * BLOCK < nt; m += PU * BLOCK) pass(m, false);
-    if (m < nt) pass(m, true);
+    table_walk<BLOCK, PU>(nt, tid, P.grouped, pass);
   } else {
     auto draw = [&](auto&& sampler) {
       for (uint32_t m = tid; m < nt; m += BLOCK) {
@@ -2130,7 +2380,7 @@ __global__ __launch_bounds__(BLOCK) void collide_batch_kernel(const BatchCav* __
 // ------------------------------------------------ faces with samples --
 // wall_kernel<PHASE> in blocks [0, 8 per_xcd) and, in the blocks after
 // them, the shared pair records of the step (sample_kernel's work, dealt to
-// lanes unless deal = 0; nb blocks per sample group): the records do not
+// lanes or not as deal says; nb blocks per sample group): the records do not
 // depend on h, so they are drawn while the face reductions (one workgroup
 // per face) leave most of the GPU idle.  Dynamic LDS: the sampler tables.
 static_assert(kWallBlock == kSampleBlock, "one block shape for faces and samples");
@@ -2155,7 +2405,30 @@ __global__ __launch_bounds__(kWallBlock) void wall_sample_kernel(Params P, const
   load_tables(P, dsm, true, T);
   __syncthreads();
   const int b = (int)blockIdx.x - nwb, group = b / nb;
-  sample_block(P, T, step, (uint32_t)group, (int64_t)(b - group * nb) * kSampleBlock, deal != 0, tidx, tcoef, sh);
+  sample_block(P, T, step, (uint32_t)group, (int64_t)(b - group * nb) * kSampleBlock, deal, tidx, tcoef, sh);
+}
+
+// wall_kernel<1> in blocks [0, 8 per_xcd) and, after them, the blocks of
+// group_kernel (nb per sample group) on the records that the launch of the x
+// faces drew: the y faces hide them.
+static_assert(kWallBlock == kGroupThreads, "one block shape for faces and groups");
+
+__global__ __launch_bounds__(kWallBlock) void wall_group_kernel(Params P, const float* __restrict__ h, int nface,
+                                                                int per_xcd, int nb, uint2* tidx, float4* tcoef) {
+  const int nwb = 8 * per_xcd;
+  if ((int)blockIdx.x < nwb) {
+    __shared__ double red[kWallBlock / 64];
+    const int f = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (f >= nface) return;
+    wall_face<1>(P, h, f + 2 * P.ny, red);
+    return;
+  }
+  extern __shared__ __align__(16) unsigned char dsm[];
+  __shared__ unsigned sh[18];
+  const int b = (int)blockIdx.x - nwb, group = b / nb;
+  const int64_t nt = P.n_pairs, at = (int64_t)(b - group * nb) * kGroupBlock, left = nt - at;
+  group_block(tidx + group * nt + at, tcoef + group * nt + at, (int)(left < kGroupBlock ? left : kGroupBlock), P.nv,
+              reinterpret_cast<unsigned*>(dsm), sh);
 }
 
 }  // namespace boltz

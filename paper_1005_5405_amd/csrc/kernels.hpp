@@ -69,6 +69,8 @@ struct Params {
   int stretched;
   // pairs from the continuous Maxwellian (Box-Muller), binned to cells
   int continuous;
+  // the shared records are rearranged by first node (group_kernel)
+  int grouped;
   // stretched spatial cells (Sec. 5.1; first-order streaming): widths of
   // the x cells and reciprocal widths along x and y, else null
   const double* wx;
@@ -87,7 +89,7 @@ struct BatchCav {
   uint2* sidx;     // where the sampler writes them (ACC_SPLIT: before the
   float4* scoef;   // sort by target half; else tidx, tcoef)
   int mode;        // accumulation of the collide increments (ACC_*)
-  int pad;
+  int records;     // what becomes of the drawn records (kRecords*)
 };
 
 // Problem of work unit u of a batched launch: the largest c with
