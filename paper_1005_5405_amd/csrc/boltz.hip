@@ -228,14 +228,11 @@ int record_mode(int mode, int64_t ngroups, int64_t ncells, int64_t nt, int nv) {
   return work >= 3.0e7 && ncells / ngroups >= 128 ? kRecordsDeal : kRecordsPlain;
 }
 
-// Accumulation mode and block sizes of the collide kernel: 64-bit
-// fixed-point accumulators for every node when they fit next to the h tile
-// and tables, else for half of the nodes per pass, else FP32; the block size
-// gives about 1024 resident threads per CU.  block[0]: pairs drawn in the
-// kernel; block[1]: pairs read from the shared table (1024 threads: 289 us
-// per collision on the 64x64 cavity against 311 us with 512).  The split
-// mode keeps 8192 / block nodes per thread in registers between its
-// passes, and uses 512 threads.
+// Accumulation mode of the collide kernel (and the block size of the modes
+// other than ACC_FIXED): 64-bit fixed-point accumulators for every node when
+// they fit next to the h tile and tables, else for half of the nodes per pass,
+// else FP32.  The split mode keeps 8192 / block nodes per thread in registers
+// between its passes, and uses 512 threads.
 bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
   int block = 256;
   if (CollideLDS::bytes(nv, ns, ACC_FIXED, true) + collide_static_lds(1024) <= kLdsBytes) mode = ACC_FIXED;
@@ -255,6 +252,23 @@ bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
     if ((b == 256 || b == 512 || b == 1024) && dyn + collide_static_lds(b) <= kLdsBytes) blocks[0] = blocks[1] = b;
   }
   return true;
+}
+
+// Threads per workgroup of the ACC_FIXED collide kernel: one workgroup of 1024
+// where the LDS or the number of cells gives a CU one cell at a time (64x64,
+// 20^3: 280 us a launch against 311 with 512; 16x16, 12^3, own pairs: step
+// 36.7 us against 37.6), two of 512 where two cells fit (32x24, 16^3, 8000
+// shared pairs: 34 us against 41 with one of 1024), three of 256 beyond (33x21,
+// 13x11x9, 3001 pairs: 20.5 us against 24.8 with 512).  128 registers a thread
+// at 1024 and 512 threads, 168 at 256.
+int collide_block(int nv, int ns, bool sampler, int64_t ncells, int ncu) {
+  const int64_t cells = (ncells + ncu - 1) / ncu;
+  auto fit = [&](int block) {
+    return (int64_t)(kLdsBytes / (CollideLDS::bytes(nv, ns, ACC_FIXED, sampler) + collide_static_lds(block)));
+  };
+  if (cells >= 3 && fit(256) >= 3) return 256;
+  if (cells >= 2 && fit(512) >= 2) return 512;
+  return 1024;
 }
 
 // Collide adjoint: false when its layout (with the sampler's tables) does
@@ -818,6 +832,8 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
                                4 * kGroupMaxNodes);
   }
   for (int t = 0; t < 2 && ea == hipSuccess && !seq; ++t) {
+    if (cmode == ACC_FIXED && !std::getenv("BOLTZ_COLLIDE_BLOCK"))
+      c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, c->ncells, ncu < 1 ? 1 : ncu);
     const void* fn = collide_fn(cblock[t], t == 1, cmode, (p->flags & BOLTZ_CONTINUOUS_PAIRS) != 0);
     c->collide_lds[t] = cmode == ACC_HYBRID ? CollideLDS::hyb_bytes(c->nv, hn[t], nsum, t == 0)
                         : cmode == ACC_PART ? CollideLDS::part_bytes(c->nv, hn[t], nsum, t == 0)
@@ -1746,7 +1762,13 @@ int boltz_batch_create(const boltz_problem* problems, int count, boltz_batch** o
       // the partial-tile layout's global rows: two per CU, one per workgroup
       if (K.part) K.cap[t] = std::min<int64_t>(K.cap[t], ncu < 1 ? 1 : ncu);
     }
-    K.block = K.ok[1] ? 512 : (K.ok[0] ? 256 : 1024);
+    // the most resident threads; of equals the smallest workgroup (20^3: 1024
+    // threads; ten cavities of 16^3..24^3: step 9.11 -> 8.39 ms)
+    for (int t = 0, most = 0; t < 3; ++t)
+      if (K.ok[t] && (int)(K.cap[t] * blocks[t] / (ncu < 1 ? 1 : ncu)) > most) {
+        most = (int)(K.cap[t] * blocks[t] / (ncu < 1 ? 1 : ncu));
+        K.block = blocks[t];
+      }
     if (e == hipSuccess && !K.ok[block_index(K.block)]) {
       boltz_batch_destroy(b);
       return bfail(nullptr, BOLTZ_EUNSUPPORTED, "boltz_batch_create: no collide block size fits a class's LDS");

@@ -920,12 +920,12 @@ __device__ __forceinline__ void scatter_part(const Part& Q, int a, int b, int as
 template <int BLOCK>
 constexpr int split_regs() { return 8192 / BLOCK; }
 
-// float4 registers per thread holding the next cell's h^s tile: 4, or with
-// 1024 threads 2 (enough for 8192 nodes), 4 for the full 24^3 tile of
+// float4 registers per thread holding the next cell's h^s tile: 4 with 256
+// threads, 3 with 512 (two cells per CU: up to 4800 nodes), or with 1024 threads 2 (enough for 8192 nodes), 4 for the full 24^3 tile of
 // ACC_HYBRID, 3 for the 20 inner slabs of ACC_PART at 24^3
 template <int BLOCK, int MODE = ACC_FIXED>
 constexpr int prefetch_regs() {
-  return BLOCK < 1024 ? 4 : (MODE == ACC_HYBRID ? 4 : (MODE == ACC_PART ? 3 : 2));
+  return BLOCK == 256 ? 4 : BLOCK < 1024 ? 3 : (MODE == ACC_HYBRID ? 4 : (MODE == ACC_PART ? 3 : 2));
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -1898,9 +1898,9 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
   const double* omx = T.om;
   const double* omy = T.om + n0;
   const double* omz = T.om + n0 + n1;
-  // node loops are unrolled where the register budget allows it (at most
-  // 256 VGPRs below 1024 threads per workgroup, 128 at 1024)
-  constexpr int NU = BLOCK <= 512 ? 4 : 1;
+  // node loops are unrolled where the register budget allows it (168 a
+  // thread at 256 threads, 128 at 512 and 1024)
+  constexpr int NU = BLOCK == 256 ? 4 : (BLOCK == 512 ? 2 : 1);
   const bool correct = !(flags & 1u);
   // node phases four nodes at a time: rows of whole z quadruples and an
   // output tile on a 16-byte boundary
@@ -2093,7 +2093,7 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
 // sample_kernel (cells of one group share them).  MODE: accumulation of the
 // increments (ACC_FIXED, ACC_SPLIT, ACC_CAS).  h_s may equal h_out.
 template <int BLOCK, bool TABLE, int MODE, int DRAW = 1>
-__global__ __launch_bounds__(BLOCK) void collide_kernel(Params P, const float* hs_g, float* hout_g, uint32_t step,
+__global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 3 : 4) void collide_kernel(Params P, const float* hs_g, float* hout_g, uint32_t step,
                                                         uint32_t flags, double* __restrict__ defect,
                                                         const uint2* __restrict__ tidx,
                                                         const float4* __restrict__ tcoef) {
@@ -2273,7 +2273,7 @@ __global__ __launch_bounds__(BLOCK) void collide_kernel(Params P, const float* h
 // shared records per thread in flight in the pair loop.  A launch covers the
 // items of one class of problems (one velocity grid).
 template <int BLOCK, int PU>
-__global__ __launch_bounds__(BLOCK) void collide_batch_kernel(const BatchCav* __restrict__ cavs,
+__global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 3 : 4) void collide_batch_kernel(const BatchCav* __restrict__ cavs,
                                                               const int2* __restrict__ items, int nitems,
                                                               const float* hin, float* hout,
                                                               const uint32_t* __restrict__ step_dev) {
