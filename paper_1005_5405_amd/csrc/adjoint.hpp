@@ -8,7 +8,6 @@
 //   stream_adj_kernel   S2    Beam-Warming sweeps transposed (order 2)
 //   order1_adj_kernel   S2    first-order unsplit step transposed
 //   lid_adj_kernel      S6    adjoint of the lid shear D
-//   grad_reduce_kernel        per-face partials -> parameter gradient
 // Adjoints are FP64, cell-major like h.  Wall parameters theta are indexed
 //   0 lid_u, 1 tau_left, 2 tau_right, 3 tau_top, 4 + ix: tau of bottom face ix.
 #pragma once
@@ -528,15 +527,6 @@ __global__ __launch_bounds__(BLOCK, 4) void collide_adj_kernel(Params P, const f
 }
 
 // ------------------------------------------------------------ walls --
-// dR/dU and dR/dtau of R = tau^-3/2 exp(|v|^2 - |v - U e_x|^2 / tau), from R.
-__device__ __forceinline__ void wall_ratio_grad(double R, double vx, double vy, double vz, double U, double tau,
-                                                double& dU, double& dtau) {
-  const double ux = vx - U;
-  const double c2 = (ux * ux + vy * vy) + vz * vz;
-  dU = R * 2.0 * ux / tau;
-  dtau = R * (c2 / (tau * tau) - 1.5 / tau);
-}
-
 __device__ __forceinline__ double face_tau(const Params& P, const WallArgs& W, int wall, int pos) {
   return wall == WALL_BOTTOM ? P.tau_b[pos] : W.tau[wall];
 }
@@ -594,7 +584,8 @@ __device__ __forceinline__ double y_face_term(const Params& P, const double* lnw
 // the last term from n_w = (A + eps B)/D, D = sum_in |v_n| w R (the sum over
 // the mirror images of the outgoing nodes, which are the incoming ones).
 // Writes lnw[f] and the partials gpart[2f] (lid velocity, top faces only)
-// and gpart[2f + 1] (the face's temperature).
+// and gpart[2f + 1] (the face's temperature); grad: null, or the gradient
+// (given to the last launch of a step).
 // Latency bound: the incoming nodes only (a range of the normal axis), four
 // per thread with their loads in flight together, 1024 threads (64x64 cavity,
 // 20^3: 13 and 16 us a launch, 25..37 with 256 threads and one node at a time).
@@ -602,9 +593,10 @@ constexpr int kWallAdjBlock = 1024;
 
 template <int PHASE>
 __global__ __launch_bounds__(kWallAdjBlock) void wall_adj_kernel(Params P, WallArgs W, const double* __restrict__ lam,
-                                                                 double* __restrict__ lnw, double* __restrict__ gpart,
-                                                                 int f0, int nface, int per_xcd) {
+                                                                 double* lnw, double* gpart, int f0, int nface,
+                                                                 int per_xcd, double* grad) {
   __shared__ double red[5 * (kWallAdjBlock / 64)];
+  __shared__ unsigned flag;
   int f = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (f >= nface) return;
   f += f0;
@@ -703,8 +695,23 @@ __global__ __launch_bounds__(kWallAdjBlock) void wall_adj_kernel(Params P, WallA
     const double l = s[0] * P.inv_eps;
     const double q = l * nw / D;
     lnw[f] = l;
-    gpart[2 * f] = (wall == WALL_TOP) ? nw * s[1] * P.inv_eps - q * s[3] : 0.0;
-    gpart[2 * f + 1] = nw * s[2] * P.inv_eps - q * s[4];
+    publish(&gpart[2 * f], (wall == WALL_TOP) ? nw * s[1] * P.inv_eps - q * s[3] : 0.0);
+    publish(&gpart[2 * f + 1], nw * s[2] * P.inv_eps - q * s[4]);
+  }
+  // the last workgroup of the last launch adds every face's partials to the
+  // gradient in a fixed order: wavefront w the wall parameter w (lid velocity
+  // from the top faces, temperatures of the left, right and top walls), then
+  // one entry per bottom face
+  if (grad && last_workgroup(P.count + 1, (uint32_t)nface, &flag)) {
+    const int w = (int)threadIdx.x >> 6;
+    if (w < 4) {
+      const int first = w == 1 ? 1 : (w == 2 ? 2 * ny + 1 : 2 * (2 * ny + nx) + (w == 3 ? 1 : 0));
+      const double t = wave_sum_of(gpart + first, nullptr, (w == 0 || w == 3) ? nx : ny, 2);
+      if ((threadIdx.x & 63) == 0) grad[w] += t;
+    }
+    for (int i = threadIdx.x; i < nx; i += kWallAdjBlock)
+      grad[4 + i] +=
+          __hip_atomic_load(&gpart[2 * (2 * ny + i) + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -925,100 +932,72 @@ __global__ __launch_bounds__(kOrder1AdjBlock) void order1_adj_kernel(Params P, c
   li[o] = out;
 }
 
-// Per-face partials into the gradient (added to grad, fixed summation order):
-// lid velocity from the top faces, the temperatures of the left, right and
-// top walls, one entry per bottom face.  faces: 1 = x faces, 2 = y faces.
-__global__ __launch_bounds__(256) void grad_reduce_kernel(Params P, const double* __restrict__ gpart,
-                                                          double* __restrict__ grad, int faces) {
-  const int nx = P.nx, ny = P.ny, t = threadIdx.x, lane = t & 63, w = t >> 6;
-  // wavefront w sums the face partials of wall parameter w, all loads of a
-  // lane issued together, then a wavefront tree sum
-  {
-    const bool on = (w == 0 || w == 3) ? (faces & 2) != 0 : (faces & 1) != 0;
-    const int n = (w == 0 || w == 3) ? nx : ny;
-    double s = 0.0;
-    if (on) {
-      for (int i = lane; i < n; i += 64) {
-        const int k = w == 0 ? 2 * (2 * ny + nx + i) : (w == 1 ? 2 * i + 1 : (w == 2 ? 2 * (ny + i) + 1
-                                                                                   : 2 * (2 * ny + nx + i) + 1));
-        s += gpart[k];
-      }
-    }
-    s = wave_sum(s);
-    if (lane == 0) grad[w] += s;
-  }
-  if (faces & 2)
-    for (int i = t; i < nx; i += blockDim.x) grad[4 + i] += gpart[2 * (2 * ny + i) + 1];
-}
-
 // ---------------------------------------------------------- lid shear --
 // Adjoint of weight * D, D = -(1/nx) sum over lid faces of 2 sum_j w_j v_x v_y
 // hhat_j with hhat the gas-side value of the top cell for v_y > 0 and the
-// wall emission with the first-order face density for v_y < 0: one
-// workgroup per top face adds its part to lam (top cells, v_y > 0 nodes)
-// and writes the face's partials gpart[2 ix] (lid velocity) and
-// gpart[2 ix + 1] (lid temperature).
-// One workgroup of kLidAdjBlock threads per top face (the three node loops
-// are latency bound: more threads per face, fewer nodes per thread).
+// wall emission with the first-order face density n_w = (A + eps B) / D for
+// v_y < 0.  One workgroup per top face adds its part to lam (top cells, v_y > 0
+// nodes; it depends on the walls alone, through the sums wlid) and, with grad,
+// forms B of its face; the last workgroup adds the faces to grad[0] (lid
+// velocity) and grad[3] (lid temperature).  Latency bound: the v_y > 0 nodes
+// only, four in flight per thread.
 constexpr int kLidAdjBlock = 1024;
 
-__global__ __launch_bounds__(kLidAdjBlock) void lid_adj_kernel(Params P, WallArgs W, const float* __restrict__ h,
-                                                               double weight, double* __restrict__ lam,
-                                                               double* __restrict__ gpart) {
-  __shared__ double red[5 * (kLidAdjBlock / 64)];
+__global__ __launch_bounds__(kLidAdjBlock) void lid_adj_kernel(Params P, const float* __restrict__ h, double weight,
+                                                               double* __restrict__ lam, double* gpart,
+                                                               double* grad) {
+  __shared__ double red[kLidAdjBlock / 64];
+  __shared__ unsigned flag;
   const int ix = blockIdx.x;
-  const int nv = P.nv, n1 = P.n[1], n2 = P.n[2];
-  const double nwt = face_density(P, h, WALL_TOP, ix, 1, 0, 0, 0, 0, red);
-  const double* R = ratio_row(P, WALL_TOP, ix);
-  const double U = W.lid_u, tau = W.tau[WALL_TOP];
+  const int n1 = P.n[1], n2 = P.n[2];
   const double c0 = weight * (-2.0 / P.nx);
-  double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  NodeWalk walk(threadIdx.x, blockDim.x, n1, n2);
-  for (int j = threadIdx.x; j < nv; j += blockDim.x, walk.next()) {
-    const int jx = walk.jx, jy = walk.jy, jz = walk.jz;
-    const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy], v3 = P.vtab[2 * kMaxAxis + jz];
-    if (!(v2 < 0.0)) continue;
-    const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
-    const double coef = c0 * w * v1 * v2;
-    const double Rj = R[j];
-    double dU, dT;
-    wall_ratio_grad(Rj, v1, v2, v3, U, tau, dU, dT);
-    const double aw = fabs(v2) * w;
-    s[0] += coef * Rj;
-    s[1] += coef * dU;
-    s[2] += coef * dT;
-    s[3] += aw * dU;
-    s[4] += aw * dT;
-  }
-  block_sum<5>(s, red);
-  const double l = s[0] * P.inv_eps;
-  const double D = wall_consts(P, WALL_TOP, ix)[1];
+  const double* k = wall_consts(P, WALL_TOP, ix);
+  const double D = k[1], l = c0 * P.wlid[1] * P.inv_eps, le = l * P.eps / D;
   double* dst = lam + cell_off(P, ix, P.ny - 1);
-  NodeWalk walk2(threadIdx.x, blockDim.x, n1, n2);
-  for (int j = threadIdx.x; j < nv; j += blockDim.x, walk2.next()) {
-    const int jx = walk2.jx, jy = walk2.jy, jz = walk2.jz;
-    const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy];
-    if (!(v2 > 0.0)) continue;
-    const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
-    dst[j] += c0 * w * v1 * v2 + l * P.eps * v2 * w / D;
-  }
-  if (threadIdx.x == 0) {
-    const double q = l * nwt / D;
-    gpart[2 * ix] = nwt * s[1] * P.inv_eps - q * s[3];
-    gpart[2 * ix + 1] = nwt * s[2] * P.inv_eps - q * s[4];
-  }
-}
-
-// Lid-shear partials into grad[0] (lid velocity) and grad[3] (lid temperature).
-__global__ void lid_grad_kernel(Params P, const double* __restrict__ gpart, double* __restrict__ grad) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double su = 0.0, st = 0.0;
-    for (int i = 0; i < P.nx; ++i) {
-      su += gpart[2 * i];
-      st += gpart[2 * i + 1];
+  const float* src = h + cell_off(P, ix, P.ny - 1);
+  const int i0 = P.vpos[1], c1 = n1 - i0, nt = P.n[0] * c1 * n2;
+  double b[1] = {0.0};
+  constexpr int NU = 4;
+  if (nt > 0) {
+    NodeWalk walk((int)threadIdx.x, kLidAdjBlock, c1, n2);
+    for (int tb = threadIdx.x; tb < nt; tb += NU * kLidAdjBlock) {
+      int js[NU], jxs[NU], jys[NU], jzs[NU];
+      double old[NU];
+      float hv[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const bool in = tb + u * kLidAdjBlock < nt;
+        jxs[u] = in ? walk.jx : 0;
+        jys[u] = in ? walk.jy + i0 : i0;
+        jzs[u] = in ? walk.jz : 0;
+        walk.next();
+        js[u] = (jxs[u] * n1 + jys[u]) * n2 + jzs[u];
+        old[u] = dst[js[u]];
+        hv[u] = grad ? src[js[u]] : 0.0f;
+      }
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if (tb + u * kLidAdjBlock >= nt) continue;
+        const double v1 = P.vtab[jxs[u]], v2 = P.vtab[kMaxAxis + jys[u]];
+        const double w = (P.omtab[jxs[u]] * P.omtab[kMaxAxis + jys[u]]) * P.omtab[2 * kMaxAxis + jzs[u]];
+        dst[js[u]] = old[u] + (c0 * w * v1 * v2 + le * v2 * w);
+        b[0] += v2 * w * (double)hv[u];
+      }
     }
-    grad[0] += su;
-    grad[3] += st;
+  }
+  if (!grad) return;
+  block_sum<1>(b, red);
+  if (threadIdx.x == 0) {
+    const double nwt = (k[0] + P.eps * b[0]) / D, q = l * nwt / D;
+    publish(&gpart[2 * ix], nwt * (c0 * P.wlid[2]) * P.inv_eps - q * P.wlid[4]);
+    publish(&gpart[2 * ix + 1], nwt * (c0 * P.wlid[3]) * P.inv_eps - q * P.wlid[5]);
+  }
+  if (last_workgroup(P.count + 1, (uint32_t)P.nx, &flag) && threadIdx.x < 64) {
+    const double su = wave_sum_of(gpart, nullptr, P.nx, 2), st = wave_sum_of(gpart + 1, nullptr, P.nx, 2);
+    if (threadIdx.x == 0) {
+      grad[0] += su;
+      grad[3] += st;
+    }
   }
 }
 

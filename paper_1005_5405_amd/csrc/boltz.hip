@@ -261,12 +261,15 @@ bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
 // shared pairs: 34 us against 41 with one of 1024), three of 256 beyond (33x21,
 // 13x11x9, 3001 pairs: 20.5 us against 24.8 with 512).  128 registers a thread
 // at 1024 and 512 threads, 168 at 256.
-int collide_block(int nv, int ns, bool sampler, int64_t ncells, int ncu) {
+// Continuous pairs drawn in the kernel need every wavefront the registers
+// allow: two of 512 there (25x67, 8x21x7, 6246 own pairs: 364 us a step
+// against 456 with three of 256).
+int collide_block(int nv, int ns, bool sampler, bool continuous, int64_t ncells, int ncu) {
   const int64_t cells = (ncells + ncu - 1) / ncu;
   auto fit = [&](int block) {
     return (int64_t)(kLdsBytes / (CollideLDS::bytes(nv, ns, ACC_FIXED, sampler) + collide_static_lds(block)));
   };
-  if (cells >= 3 && fit(256) >= 3) return 256;
+  if (cells >= 3 && fit(256) >= 3 && !(sampler && continuous)) return 256;
   if (cells >= 2 && fit(512) >= 2) return 512;
   return 1024;
 }
@@ -677,6 +680,8 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   const size_t o_wconst_b = off; off = align256(off + (size_t)p->nx * 2 * 8);
   const size_t o_dpart = off; off = align256(off + (size_t)p->nx * 8);
   const size_t o_wconst = off; off = align256(off + 8 * 8);
+  const size_t o_wlid = off; off = align256(off + 6 * 8);
+  const size_t o_count = off; off = align256(off + 2 * 4);
   const size_t o_status = off; off = align256(off + 4);
   const size_t o_lnw = off; off = align256(off + (size_t)nfaces * 8);
   const size_t o_gpart = off; off = align256(off + (size_t)nfaces * 2 * 8);
@@ -788,6 +793,8 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   P.wconst_b = reinterpret_cast<double*>(base + o_wconst_b);
   P.dpart = reinterpret_cast<double*>(base + o_dpart);
   P.wconst = reinterpret_cast<double*>(base + o_wconst);
+  P.wlid = reinterpret_cast<double*>(base + o_wlid);
+  P.count = reinterpret_cast<uint32_t*>(base + o_count);
   P.status = reinterpret_cast<uint32_t*>(base + o_status);
   P.hyb_lo = hlo[1];
   P.hyb_n = hn[1];
@@ -833,7 +840,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   }
   for (int t = 0; t < 2 && ea == hipSuccess && !seq; ++t) {
     if (cmode == ACC_FIXED && !std::getenv("BOLTZ_COLLIDE_BLOCK"))
-      c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, c->ncells, ncu < 1 ? 1 : ncu);
+      c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, P.continuous != 0, c->ncells, ncu < 1 ? 1 : ncu);
     const void* fn = collide_fn(cblock[t], t == 1, cmode, (p->flags & BOLTZ_CONTINUOUS_PAIRS) != 0);
     c->collide_lds[t] = cmode == ACC_HYBRID ? CollideLDS::hyb_bytes(c->nv, hn[t], nsum, t == 0)
                         : cmode == ACC_PART ? CollideLDS::part_bytes(c->nv, hn[t], nsum, t == 0)
@@ -1261,9 +1268,13 @@ int boltz_moments(boltz_ctx* c, const float* h, const boltz_walls* walls, double
     const int rc = ensure_ratio(c, W, walls, st);
     if (rc != BOLTZ_OK) return rc;
   }
-  hipLaunchKernelGGL(moments_kernel, dim3((unsigned)c->ncells), dim3(kMomentsBlock), 0, st, c->P, W, h, mom,
-                     lid_shear ? 1 : 0);
-  if (lid_shear) hipLaunchKernelGGL(lid_reduce_kernel, dim3(1), dim3(64), 0, st, c->P, lid_shear);
+  const bool stage = c->n[2] % 4 == 0 && (reinterpret_cast<uintptr_t>(h) & 15) == 0 && c->nv <= kMomentsStage;
+  if (stage)
+    hipLaunchKernelGGL(moments_kernel<true>, dim3((unsigned)c->ncells), dim3(kMomentsBlock), (size_t)c->nv * 4, st,
+                       c->P, h, mom, lid_shear);
+  else
+    hipLaunchKernelGGL(moments_kernel<false>, dim3((unsigned)c->ncells), dim3(kMomentsBlock), 0, st, c->P, h, mom,
+                       lid_shear);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "moments_kernel launch");
 }
@@ -1278,16 +1289,16 @@ static int launch_stream_adj(boltz_ctx* c, const WallArgs& W, const double* lo, 
                              hipStream_t st) {
   const bool cavity = c->p.bc == BOLTZ_BC_CAVITY;
   const int nx = c->p.nx, ny = c->p.ny;
-  auto walls_adj = [&](auto kern, int f0, int nface) {
+  auto walls_adj = [&](auto kern, int f0, int nface, double* g) {
     const int per_xcd = (nface + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(kWallAdjBlock), 0, st, c->P, W, lo, c->lnw, c->gpart, f0, nface,
-                       per_xcd);
+                       per_xcd, g);
   };
   if (c->p.order == 2) {
     // the x faces' terms pass through the y sweep, hence after the y faces
     if (cavity) {
-      walls_adj(wall_adj_kernel<0>, 2 * ny, 2 * nx);
-      walls_adj(wall_adj_kernel<1>, 0, 2 * ny);
+      walls_adj(wall_adj_kernel<0>, 2 * ny, 2 * nx, nullptr);
+      walls_adj(wall_adj_kernel<1>, 0, 2 * ny, grad);
     }
     const int tiles_x = (nx + kATX - 1) / kATX, tiles_y = (ny + kATY - 1) / kATY;
     const long long units = stream_adj_units(nx, ny, c->nv);
@@ -1302,12 +1313,11 @@ static int launch_stream_adj(boltz_ctx* c, const WallArgs& W, const double* lo, 
       hipLaunchKernelGGL(stream_adj_kernel<1>, grid, dim3(kATY * kAJ), 0, st, c->P, lo, li, c->lnw, tiles_x, tiles_y,
                          (int)units, per_xcd);
   } else {
-    if (cavity) walls_adj(wall_adj_kernel<0>, 0, 2 * (nx + ny));
+    if (cavity) walls_adj(wall_adj_kernel<0>, 0, 2 * (nx + ny), grad);
     const int nc = (c->nv + kOrder1AdjBlock - 1) / kOrder1AdjBlock;
     hipLaunchKernelGGL(order1_adj_kernel, dim3((unsigned)(c->ncells * nc)), dim3(kOrder1AdjBlock), 0, st, c->P, lo,
                        li, c->lnw, nc);
   }
-  if (cavity && grad) hipLaunchKernelGGL(grad_reduce_kernel, dim3(1), dim3(256), 0, st, c->P, c->gpart, grad, 3);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "stream adjoint launch");
 }
@@ -1417,9 +1427,8 @@ int boltz_lid_shear_adjoint(boltz_ctx* c, const float* h, const boltz_walls* wal
   const WallArgs W = make_walls(walls);
   const int rc = ensure_ratio(c, W, walls, st);
   if (rc != BOLTZ_OK) return rc;
-  hipLaunchKernelGGL(lid_adj_kernel, dim3((unsigned)c->p.nx), dim3(kLidAdjBlock), 0, st, c->P, W, h, weight, lam,
-                     c->gpart);
-  if (grad_walls) hipLaunchKernelGGL(lid_grad_kernel, dim3(1), dim3(64), 0, st, c->P, c->gpart, grad_walls);
+  hipLaunchKernelGGL(lid_adj_kernel, dim3((unsigned)c->p.nx), dim3(kLidAdjBlock), 0, st, c->P, h, weight, lam,
+                     c->gpart, grad_walls);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "lid shear adjoint launch");
 }

@@ -58,6 +58,9 @@ struct Params {
   double* dpart;          // [nx] lid shear partial sums
   double* wconst;         // [4][2] per wall: A_w, D_w of the face densities
   double* wconst_b;       // [nx][2] A, D of every bottom face
+  double* wlid;           // [6] sums over the lid's incoming nodes (v_y < 0): w v_x v_y
+                          // times 1, R, dR/dU, dR/dtau, then |v_y| w times dR/dU, dR/dtau
+  uint32_t* count;        // [2] finished workgroups (zero between launches)
   uint32_t* status;       // device status bits
   // ACC_HYBRID collisions: nodes hyb_lo .. hyb_lo + hyb_n - 1 (whole
   // x-slabs) take 64-bit accumulators, the others FP32; hyb_ovf: one row of
@@ -126,6 +129,52 @@ __device__ __forceinline__ double wall_ratio(double vx, double vy, double vz, do
   return tfac * exp(v2 - c2 / tau);
 }
 
+// dR/dU and dR/dtau of R = tau^-3/2 exp(|v|^2 - |v - U e_x|^2 / tau), from R.
+__device__ __forceinline__ void wall_ratio_grad(double R, double vx, double vy, double vz, double U, double tau,
+                                                double& dU, double& dtau) {
+  const double ux = vx - U;
+  const double c2 = (ux * ux + vy * vy) + vz * vz;
+  dU = R * 2.0 * ux / tau;
+  dtau = R * (c2 / (tau * tau) - 1.5 / tau);
+}
+
+// A value for the last workgroup of this launch (below): written at the
+// device's point of coherence, complete before the function returns.
+__device__ __forceinline__ void publish(double* p, double v) {
+  (void)__hip_atomic_exchange(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0);
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// Whether this workgroup is the last of `total` to get here (one call each):
+// the values that thread 0 of the others published before are then there to
+// be read (wave_sum_of).  Only atomics of device scope take part: a fence
+// would write back the L2 (10 us a launch).  Leaves the counter at zero.
+// flag: a word of LDS.
+__device__ __forceinline__ bool last_workgroup(uint32_t* count, uint32_t total, unsigned* flag) {
+  if (threadIdx.x == 0) {
+    const bool last =
+        __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1u;
+    if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *flag = last ? 1u : 0u;
+  }
+  __syncthreads();
+  return *flag != 0u;
+}
+
+// Sum of x[i] (times w[i] unless w is null) over i < n by one wavefront, in a
+// fixed order; x written by other workgroups of the same launch.
+__device__ __forceinline__ double wave_sum_of(const double* x, const double* w, int n, int stride = 1) {
+  double t = 0.0;
+  for (int i = (int)(threadIdx.x & 63); i < n; i += 64) {
+    const double v = __hip_atomic_load(x + (int64_t)i * stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    t += w ? w[i] * v : v;
+  }
+  return wave_sum(t);
+}
+
 // Re-emitted deviation h_w = (n_w Phi_w/Phi0 - 1)/eps, stored in FP32.
 __device__ __forceinline__ float ghost_value(double nw, double R, double inv_eps) {
   return (float)((nw * R - 1.0) * inv_eps);
@@ -168,68 +217,6 @@ __device__ __forceinline__ float xswept_value(const Params& P, const float* h, i
   return bw_update(h0, hn[0], hn[1], P.cour[jx], P.cour2[jx]);
 }
 
-// Density n_w of one face.  A = sum_out |v_n| w_j, D = sum over the mirror
-// images of the outgoing nodes of |v_n| w R (same order as A, so a wall at
-// rest facing h = 0 gives n_w = 1 exactly), B = sum_out |v_n| w_j hhat_j;
-// n_w = (A + eps B) / D.  `order` selects the face value: 1 = adjacent cell,
-// 2 = Beam-Warming face value, from the x-swept state for y faces.
-__device__ __forceinline__ double face_density(const Params& P, const float* h, int wall, int pos,
-                               int order, double nwl0, double nwl1, double nwr0, double nwr1,
-                               double* red) {
-  const int nx = P.nx, ny = P.ny, nv = P.nv, n1 = P.n[1], n2 = P.n[2];
-  const int nax = (wall <= WALL_RIGHT) ? 0 : 1;
-  const int sgn = (wall == WALL_LEFT || wall == WALL_BOTTOM) ? 1 : -1;
-  int ax_, ay_, bx_, by_;
-  switch (wall) {
-    case WALL_LEFT: ax_ = 0; ay_ = pos; bx_ = 1; by_ = pos; break;
-    case WALL_RIGHT: ax_ = nx - 1; ay_ = pos; bx_ = nx - 2; by_ = pos; break;
-    case WALL_BOTTOM: ax_ = pos; ay_ = 0; bx_ = pos; by_ = 1; break;
-    default: ax_ = pos; ay_ = ny - 1; bx_ = pos; by_ = ny - 2; break;
-  }
-  const double dl = nax ? P.dy : P.dx;
-  const bool ysw = (order == 2) && (nax == 1);
-  double s[3] = {0.0, 0.0, 0.0};
-  // four nodes per thread and pass, so that their loads are in flight together
-  constexpr int U = 4;
-  const int step = blockDim.x;
-  NodeWalk walk(threadIdx.x, step, n1, n2);
-  for (int j0 = threadIdx.x; j0 < nv; j0 += U * step) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * step;
-      const int jx = walk.jx, jy = walk.jy, jz = walk.jz;
-      walk.next();
-      if (j >= nv) continue;
-      const double vn = nax ? P.vtab[kMaxAxis + jy] : P.vtab[jx];
-      if (!(sgn * vn < 0.0)) continue;
-      const double an = fabs(vn);
-      const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
-      int mx = jx, my = jy;
-      if (nax == 0) mx = P.n[0] - 1 - jx; else my = n1 - 1 - jy;
-      const double R = ratio_row(P, wall, pos)[(mx * n1 + my) * n2 + jz];
-      double ha, hb = 0.0;
-      if (ysw) {
-        ha = xswept_value(P, h, ax_, ay_, j, jx, jy, jz, nwl0, nwr0);
-        hb = xswept_value(P, h, bx_, by_, j, jx, jy, jz, nwl1, nwr1);
-      } else {
-        ha = h[cell_off(P, ax_, ay_) + j];
-        if (order == 2) hb = h[cell_off(P, bx_, by_) + j];
-      }
-      double hh = ha;
-      if (order == 2) {
-        const double C = an * P.dt / dl;
-        hh = ha + 0.5 * (1.0 - C) * (ha - hb);
-      }
-      const double aw = an * w;
-      s[0] += aw;
-      s[1] += aw * R;
-      s[2] += aw * hh;
-    }
-  }
-  block_sum<3>(s, red);
-  return (s[0] + P.eps * s[2]) / s[1];
-}
-
 // One workgroup per wall (left, right, top) and per bottom face: the table
 // Phi_w / Phi0 of every node (FP64; only the lid moves, with velocity lid_u
 // along x), then A = sum_out |v_n| w_j and D = sum over the mirror images of
@@ -241,7 +228,7 @@ constexpr int kWallConstBlock = 1024;
 // Blocks first, first + 1, ... of the full set (0 left, 1 right, 2 top, 3 +
 // i bottom face i): a change of the lid alone rebuilds block 2 only.
 __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, WallArgs W, int first) {
-  __shared__ double red[2 * (kWallConstBlock / 64)];
+  __shared__ double red[8 * (kWallConstBlock / 64)];
   const int b = (int)blockIdx.x + first;
   const int wall = b == 0 ? WALL_LEFT : (b == 1 ? WALL_RIGHT : (b == 2 ? WALL_TOP : WALL_BOTTOM));
   const int pos = b < 3 ? 0 : b - 3;
@@ -250,15 +237,31 @@ __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, Wa
   const double tau = wall == WALL_BOTTOM ? P.tau_b[pos] : W.tau[wall];
   const double tfac = wall == WALL_BOTTOM ? pow(tau, -1.5) : W.tfac[wall];
   double* R = const_cast<double*>(ratio_row(P, wall, pos));
+  double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int j = threadIdx.x; j < nv; j += blockDim.x) {
     int jx, jy, jz;
     node_decode(j, n1, n2, jx, jy, jz);
-    R[j] = wall_ratio(P.vtab[jx], P.vtab[kMaxAxis + jy], P.vtab[2 * kMaxAxis + jz], Uw, tau, tfac);
+    const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy], v3 = P.vtab[2 * kMaxAxis + jz];
+    const double Rj = wall_ratio(v1, v2, v3, Uw, tau, tfac);
+    R[j] = Rj;
+    if (wall == WALL_TOP && v2 < 0.0) {
+      // the lid's part of the shear on it and of its derivatives, which
+      // depend on the walls alone
+      const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
+      double dU, dT;
+      wall_ratio_grad(Rj, v1, v2, v3, Uw, tau, dU, dT);
+      const double c = w * v1 * v2, aw = fabs(v2) * w;
+      s[2] += c;
+      s[3] += c * Rj;
+      s[4] += c * dU;
+      s[5] += c * dT;
+      s[6] += aw * dU;
+      s[7] += aw * dT;
+    }
   }
   __syncthreads();
   const int nax = (wall <= WALL_RIGHT) ? 0 : 1;
   const int sgn = (wall == WALL_LEFT || wall == WALL_BOTTOM) ? 1 : -1;
-  double s[2] = {0.0, 0.0};
   for (int j = threadIdx.x; j < nv; j += blockDim.x) {
     int jx, jy, jz;
     node_decode(j, n1, n2, jx, jy, jz);
@@ -270,16 +273,20 @@ __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, Wa
     s[0] += aw;
     s[1] += aw * R[(mx * n1 + my) * n2 + jz];
   }
-  block_sum<2>(s, red);
+  if (wall == WALL_TOP) block_sum<8>(s, red);
+  else block_sum<2>(reinterpret_cast<double(&)[2]>(s), red);
   if (threadIdx.x == 0) {
     double* k = const_cast<double*>(wall_consts(P, wall, pos));
     k[0] = s[0];
     k[1] = s[1];
+    if (wall == WALL_TOP)
+      for (int i = 0; i < 6; ++i) P.wlid[i] = s[2 + i];
   }
 }
 
 // B of one face: sum over the outgoing nodes of |v_n| w_j hhat_j (hhat as in
-// face_density).  The outgoing nodes (a range of the normal axis) are
+// the scheme: the adjacent cell's h, or the Beam-Warming face value, for y
+// faces of the x-swept state).  The outgoing nodes (a range of the normal axis) are
 // numbered t = 0, 1, ... in velocity order; this thread takes t = j0, j0 +
 // step, ..., U nodes per pass with every load of a pass issued before it
 // is used.  A y face of order 2 away from the corner columns reads the three
@@ -832,24 +839,51 @@ namespace boltz {
 // One workgroup per cell.  The 11 sums w h {1, v, |v|^2, v_i v_k} come from
 // z moments Z_p = sum_z omega_z v_z^p h (p <= 2) of each velocity row (one
 // row per thread, the factors omega_z v_z^p from the table zmom through
-// scalar loads, rows read four nodes at a time when nv_z % 4 == 0), then
-// the row's terms: W = omega_x omega_y, a = v_x, b = v_y.
+// scalar loads), then the row's terms: W = omega_x omega_y, a = v_x, b = v_y.
+// Bound by HBM (4 B a node): the cell is read in 16-byte pieces of
+// consecutive threads, all in flight together, into LDS (LDS_STAGE), where a
+// row per thread has no bank conflicts; cells too large for 64 KB, or of odd
+// sizes, are read row by row.  The lid shear takes two more sums of the top
+// row of cells over v_y > 0 (w v_x v_y h, and w v_y h for the
+// lid's density n_w = (A + eps B) / D); the re-emitted part is n_w times a sum
+// that depends on the walls alone (wlid).  The last workgroup of the top row
+// adds the faces.  64x64 cells, 20^3: 35 us with the lid (3.8 TB/s), 41 + 5 with rows
+// read in place, a node loop per lid face and a launch to add the faces.
 constexpr int kMomentsBlock = 512;
+constexpr int kMomentsStage = 15872;  // largest cell staged: 62 KB, under 64 KB with the block sums
 
-__global__ __launch_bounds__(kMomentsBlock) void moments_kernel(Params P, WallArgs W, const float* __restrict__ h,
-                                                                double* __restrict__ mom, int want_lid) {
+template <bool LDS_STAGE>
+__global__ __launch_bounds__(kMomentsBlock) void moments_kernel(Params P, const float* __restrict__ h,
+                                                                double* __restrict__ mom, double* lid) {
+  extern __shared__ __align__(16) unsigned char dsm[];
   __shared__ double red[20 * (kMomentsBlock / 64)];
+  __shared__ unsigned flag;
   const int nv = P.nv, n0 = P.n[0], n1 = P.n[1], n2 = P.n[2];
-  // the top row first: its workgroups also sum the lid face (longer), so
-  // they start before the others rather than trail them
+  // the top row first: its last workgroup also adds the lid faces
   const int64_t ncells = (int64_t)P.nx * P.ny;
   const int64_t cell = ((int64_t)blockIdx.x + (int64_t)(P.ny - 1) * P.nx) % ncells;
   const float* src = h + cell * nv;
   const const_f64* zc = (const const_f64*)P.zmom;
-  const bool vec = (n2 & 3) == 0 && ((reinterpret_cast<uintptr_t>(src) & 15) == 0);
-  double s[11];
+  const bool vec = LDS_STAGE || ((n2 & 3) == 0 && ((reinterpret_cast<uintptr_t>(src) & 15) == 0));
+  const f32x4* rows = reinterpret_cast<const f32x4*>(LDS_STAGE ? (const void*)dsm : (const void*)src);
+  if constexpr (LDS_STAGE) {
+    const f32x4* g4 = reinterpret_cast<const f32x4*>(src);
+    f32x4* t4 = reinterpret_cast<f32x4*>(dsm);
+    const int nv4 = nv >> 2;
+    constexpr int U = 4;
+    for (int i0 = threadIdx.x; i0 < nv4; i0 += U * kMomentsBlock) {
+      f32x4 v[U];
 #pragma unroll
-  for (int i = 0; i < 11; ++i) s[i] = 0.0;
+      for (int u = 0; u < U; ++u) v[u] = g4[min(i0 + u * kMomentsBlock, nv4 - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * kMomentsBlock < nv4) t4[i0 + u * kMomentsBlock] = v[u];
+    }
+    __syncthreads();
+  }
+  double s[13];
+#pragma unroll
+  for (int i = 0; i < 13; ++i) s[i] = 0.0;
   for (int row = threadIdx.x; row < n0 * n1; row += kMomentsBlock) {
     const int jx = row / n1, jy = row - (row / n1) * n1;
     double Z0 = 0.0, Z1 = 0.0, Z2 = 0.0;
@@ -861,7 +895,7 @@ __global__ __launch_bounds__(kMomentsBlock) void moments_kernel(Params P, WallAr
       Z2 = fma(z[2], x, Z2);
     };
     if (vec) {
-      const f32x4* r4 = reinterpret_cast<const f32x4*>(src + row * n2);
+      const f32x4* r4 = rows + ((row * n2) >> 2);
       for (int q = 0; q < (n2 >> 2); ++q) {
         const f32x4 v = r4[q];
         node(4 * q, v.x);
@@ -884,22 +918,28 @@ __global__ __launch_bounds__(kMomentsBlock) void moments_kernel(Params P, WallAr
     s[8] += (b * b) * T0;
     s[9] += b * T1;
     s[10] += Wr * Z2;
+    if (b > 0.0) {
+      s[11] += (a * b) * T0;
+      s[12] += b * T0;
+    }
   }
   s[4] = (s[5] + s[8]) + s[10];
   {
-    // block sums through the 20-value wavefront fold (lanes 0..10 of
+    // block sums through the 20-value wavefront fold (lanes 0..12 of
     // wavefront 0 receive the totals), then broadcast in wavefront 0
     double v[20];
 #pragma unroll
-    for (int i = 0; i < 20; ++i) v[i] = i < 11 ? s[i] : 0.0;
+    for (int i = 0; i < 20; ++i) v[i] = i < 13 ? s[i] : 0.0;
     const int rows = n0 * n1;
     const int nwd = rows >= kMomentsBlock ? kMomentsBlock / 64 : (rows + 63) / 64;
     const double t = block_sum20_w0<kMomentsBlock>(v, red, nwd);
     if (threadIdx.x < 64) {
 #pragma unroll
-      for (int i = 0; i < 11; ++i) s[i] = lane_value(t, i);
+      for (int i = 0; i < 13; ++i) s[i] = lane_value(t, i);
     }
   }
+  const int iy = (int)(cell / P.nx), ix = (int)(cell % P.nx);
+  const bool face = lid && iy == P.ny - 1;
   if (threadIdx.x == 0) {
     // V0 units: n = 1 + eps rho, u = U/n, theta = ((2/3)E - rho)/n - (2/3) eps |u|^2,
     // Pi_ij = 2 P_ij - 2 eps n u_i u_j
@@ -915,43 +955,18 @@ __global__ __launch_bounds__(kMomentsBlock) void moments_kernel(Params P, WallAr
     o[4] = ((2.0 / 3.0) * s[4] - rho) / n - (2.0 / 3.0) * eps * uu;
     const int ik[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
     for (int k = 0; k < 6; ++k) o[5 + k] = 2.0 * s[5 + k] - 2.0 * eps * n * u[ik[k][0]] * u[ik[k][1]];
-  }
-  const int iy = (int)(cell / P.nx), ix = (int)(cell % P.nx);
-  if (want_lid && iy == P.ny - 1) {
-    // lid face: gas-side values of this top cell for v_y > 0, wall emission
-    // with the first-order face density for v_y < 0
-    __syncthreads();  // red is reused
-    const double nwt = face_density(P, h, WALL_TOP, ix, 1, 0, 0, 0, 0, red);
-    // Phi_w / Phi0 of the lid from its table (built for these walls; the
-    // same values wall_ratio gives)
-    const double* R = ratio_row(P, WALL_TOP, ix);
-    double pxy[1] = {0.0};
-    for (int j = threadIdx.x; j < nv; j += blockDim.x) {
-      int jx, jy, jz;
-      node_decode(j, n1, n2, jx, jy, jz);
-      const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy];
-      const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
-      double hh = 0.0;
-      if (v2 > 0.0) hh = (double)src[j];
-      else if (v2 < 0.0) hh = (nwt * R[j] - 1.0) * P.inv_eps;
-      pxy[0] += w * v1 * v2 * hh;
+    if (face) {
+      // lid face: gas-side values of this top cell for v_y > 0, wall emission
+      // with the first-order face density for v_y < 0
+      const double* k = wall_consts(P, WALL_TOP, ix);
+      const double nwt = (k[0] + eps * s[12]) / k[1];
+      publish(&P.dpart[ix], 2.0 * (s[11] + (nwt * P.wlid[1] - P.wlid[0]) * P.inv_eps));
     }
-    block_sum<1>(pxy, red);
-    if (threadIdx.x == 0) P.dpart[ix] = 2.0 * pxy[0];
   }
-}
-
-__global__ void lid_reduce_kernel(Params P, double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double t = 0.0;
-    if (P.wx) {
-      // stretched cells: the faces weighted by their lengths
-      for (int i = 0; i < P.nx; ++i) t += P.wx[i] * P.dpart[i];
-      *out = -t;
-    } else {
-      for (int i = 0; i < P.nx; ++i) t += P.dpart[i];
-      *out = -t / P.nx;
-    }
+  // the faces weighted by their lengths (stretched cells), else their mean
+  if (face && last_workgroup(P.count, (uint32_t)P.nx, &flag) && threadIdx.x < 64) {
+    const double t = wave_sum_of(P.dpart, P.wx, P.nx);
+    if (threadIdx.x == 0) *lid = P.wx ? -t : -t / P.nx;
   }
 }
 
