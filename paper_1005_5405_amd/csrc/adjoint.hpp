@@ -142,19 +142,6 @@ __host__ __device__ inline size_t collide_adj_lds(int nv, int ns, bool sampler, 
 // static LDS of the collide adjoint (maxima per wavefront, flag)
 __host__ __device__ inline size_t collide_adj_static_lds(int block) { return 8 * (size_t)(block / 64) + 16; }
 
-// Sum of 5 values per lane over the wavefront: lane 32 b5 + 16 b4 + 8 b3
-// holds value k = 3 b5 + 2 b4 + b3 (valid where 2 b4 + b3 < 3 - b5).
-__device__ __forceinline__ double wave_fold5(double (&v)[5], int lane) {
-  fold_half<5, 32, 0>(v, lane);
-  fold_half<3, 16, 0>(v, lane);
-  fold_half<2, 8, kDppMirror>(v, lane);
-  double t = v[0];
-  t += dpp_f64<kDppHalfMirror>(t);
-  t += dpp_f64<kDppXor2>(t);
-  t += dpp_f64<kDppXor1>(t);
-  return t;
-}
-
 // Largest value over the wavefront, in every lane (no LDS traffic).
 __device__ __forceinline__ double wave_max(double v) {
   v = fmax(v, dpp_f64<kDppXor1>(v));

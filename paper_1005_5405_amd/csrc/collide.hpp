@@ -1289,7 +1289,8 @@ struct ZQuad {
   }
 };
 
-template <int BLOCK>
+// DIFF = false: h^s is not read and acc[15..20) are left zero.
+template <int BLOCK, bool DIFF = true>
 __device__ __forceinline__ void correction_sums(const TablesLDS& T, const double* zmom, const float* hs,
                                                 const float* hc_t, int n0, int n1, int n2, double (&acc)[20]) {
   const double* vx = T.v;
@@ -1305,15 +1306,17 @@ __device__ __forceinline__ void correction_sums(const TablesLDS& T, const double
     double S0 = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0, R0 = 0.0, R1 = 0.0, R2 = 0.0;
     auto node = [&](int jz, float hcf, float hsf) {
       const const_f64* z = zc + 8 * jz;
-      const double hc = (double)hcf, d = hc - (double)hsf;
+      const double hc = (double)hcf, d = DIFF ? hc - (double)hsf : 0.0;
       S0 = fma(z[0], hc, S0);
       S1 = fma(z[1], hc, S1);
       S2 = fma(z[2], hc, S2);
       S3 = fma(z[3], hc, S3);
       S4 = fma(z[4], hc, S4);
-      R0 = fma(z[0], d, R0);
-      R1 = fma(z[1], d, R1);
-      R2 = fma(z[2], d, R2);
+      if (DIFF) {
+        R0 = fma(z[0], d, R0);
+        R1 = fma(z[1], d, R1);
+        R2 = fma(z[2], d, R2);
+      }
     };
     if (vec) {
       const f32x4* hcr = reinterpret_cast<const f32x4*>(hc_t + row * n2);
@@ -1321,23 +1324,26 @@ __device__ __forceinline__ void correction_sums(const TablesLDS& T, const double
       for (int q = 0; q < (n2 >> 2); ++q) {
         ZQuad zq;
         zq.load(zc, 4 * q);
-        const f32x4 c4 = hcr[q], s4 = hsr[q];
+        const f32x4 c4 = hcr[q], s4 = DIFF ? hsr[q] : c4;
         const float hcq[4] = {c4.x, c4.y, c4.z, c4.w}, hsq[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const double hc = (double)hcq[k], d = hc - (double)hsq[k];
+          const double hc = (double)hcq[k];
           S0 = fma(zq.f[k][0], hc, S0);
           S1 = fma(zq.f[k][1], hc, S1);
           S2 = fma(zq.f[k][2], hc, S2);
           S3 = fma(zq.f[k][3], hc, S3);
           S4 = fma(zq.f[k][4], hc, S4);
-          R0 = fma(zq.f[k][0], d, R0);
-          R1 = fma(zq.f[k][1], d, R1);
-          R2 = fma(zq.f[k][2], d, R2);
+          if (DIFF) {
+            const double d = hc - (double)hsq[k];
+            R0 = fma(zq.f[k][0], d, R0);
+            R1 = fma(zq.f[k][1], d, R1);
+            R2 = fma(zq.f[k][2], d, R2);
+          }
         }
       }
     } else {
-      for (int jz = 0; jz < n2; ++jz) node(jz, hc_t[row * n2 + jz], hs[row * n2 + jz]);
+      for (int jz = 0; jz < n2; ++jz) node(jz, hc_t[row * n2 + jz], DIFF ? hs[row * n2 + jz] : 0.0f);
     }
     const double W = omx[jx] * omy[jy], a = vx[jx], b = vy[jy], c2 = a * a + b * b;
     const double T0 = W * S0, T1 = W * S1, T2 = W * S2, T3 = W * S3, T4 = W * S4;
@@ -1357,12 +1363,14 @@ __device__ __forceinline__ void correction_sums(const TablesLDS& T, const double
     acc[12] += T2;
     acc[13] += c2 * T1 + T3;
     acc[14] += (c2 * c2) * T0 + 2.0 * c2 * T2 + T4;
-    const double Q0 = W * R0, Q1 = W * R1, Q2 = W * R2;
-    acc[15] += Q0;
-    acc[16] += a * Q0;
-    acc[17] += b * Q0;
-    acc[18] += Q1;
-    acc[19] += c2 * Q0 + Q2;
+    if (DIFF) {
+      const double Q0 = W * R0, Q1 = W * R1, Q2 = W * R2;
+      acc[15] += Q0;
+      acc[16] += a * Q0;
+      acc[17] += b * Q0;
+      acc[18] += Q1;
+      acc[19] += c2 * Q0 + Q2;
+    }
   }
 }
 

@@ -342,9 +342,19 @@ __device__ __forceinline__ void seq_moments(const double* vx, const double* vy, 
       for (int k = 0; k < 4; ++k)
 #pragma unroll
         for (int p = 0; p < 3; ++p) z[k][p] = zc[8 * (jz + k) + p];
+      // rows of whole quadruples: one 16-byte read, no bank conflicts between
+      // neighbouring rows (single words at a stride of 20 take eight passes)
+      float hv[4];
+      if ((n2 & 3) == 0) {
+        const f32x4 t = *reinterpret_cast<const f32x4*>(h + row * n2 + jz);
+        hv[0] = t.x; hv[1] = t.y; hv[2] = t.z; hv[3] = t.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) hv[k] = h[row * n2 + jz + k];
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const double v = (double)h[row * n2 + jz + k];
+        const double v = (double)hv[k];
         S0 = fma(z[k][0], v, S0);
         S1 = fma(z[k][1], v, S1);
         S2 = fma(z[k][2], v, S2);
@@ -364,7 +374,21 @@ __device__ __forceinline__ void seq_moments(const double* vx, const double* vy, 
     s[3] += W * S1;
     s[4] += (a * a + b * b) * T0 + W * S2;
   }
-  block_sum<5, kSeqBlock>(s, red);
+  // block sums: the five values folded within each wavefront by lane swaps
+  constexpr int NW = kSeqBlock / 64;
+  const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
+  const double t = wave_fold5(s, lane);
+  const int b5 = lane >> 5, pos = 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
+  if ((lane & 7) == 0 && pos < 3 - b5) red[(3 * b5 + pos) * NW + wid] = t;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v += red[i * NW + w];
+    s[i] = v;
+  }
+  __syncthreads();
 }
 
 // Grid: one workgroup of kSeqBlock threads per cell.  vom: node velocities
@@ -372,7 +396,12 @@ __device__ __forceinline__ void seq_moments(const double* vx, const double* vy, 
 // Records of the cell's sample group as left by seq_level_kernel (SCHED 1,
 // schedule S) or seq_level64_kernel (SCHED 0, levels lev).  The node
 // phases use the whole workgroup; the pair loop, a chain of dependent LDS
-// accesses, runs on wavefront 0 while the others wait at a barrier.
+// accesses, runs on wavefront 0 while the others wait at a barrier.  Bound by
+// that chain's latency and the node phases' (five cells per CU).  160x160
+// cells, 20^3, 6144 continuous pairs, whole step: 1.78 ms with single-word
+// moment reads, shuffle reductions and differences of h^s formed but not
+// used; 1.64 without; 1.63 with the chain's wavefront ahead in priority;
+// 1.58 with the eight steps of a pass in one block.
 template <int SCHED>
 __global__ __launch_bounds__(kSeqBlock, 5) void seq_collide_kernel(
     Params P, const double* __restrict__ vom, const float* __restrict__ hs_all, float* __restrict__ hout_all,
@@ -403,13 +432,25 @@ __global__ __launch_bounds__(kSeqBlock, 5) void seq_collide_kernel(
   if (vec4) {
     const f32x4* s4 = reinterpret_cast<const f32x4*>(hs);
     f32x4* t4 = reinterpret_cast<f32x4*>(tile);
-    for (int i = tid; i < (nv >> 2); i += kSeqBlock) t4[i] = __builtin_nontemporal_load(&s4[i]);
+    // four loads of a thread in flight together
+    const int nv4 = nv >> 2;
+    for (int i0 = tid; i0 < nv4; i0 += 4 * kSeqBlock) {
+      f32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(&s4[min(i0 + u * kSeqBlock, nv4 - 1)]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i0 + u * kSeqBlock < nv4) t4[i0 + u * kSeqBlock] = v[u];
+    }
   } else {
     for (int j = tid; j < nv; j += kSeqBlock) tile[j] = hs[j];
   }
   __syncthreads();
   double ms[5];
   seq_moments(vx, vy, omx, omy, P.zmom, tile, n0, n1, n2, red, ms);
+  // the chain's wavefront issues before those in the node phases of the CU's
+  // other cells
+  __builtin_amdgcn_s_setprio(3);
   // ---- S3 + S4: the records in order, one level of a group at a time
   if (SCHED == 0 && tid < 64) {
     const int64_t nt = P.n_pairs, ngr = (nt + kSeqGroup64 - 1) / kSeqGroup64;
@@ -523,28 +564,30 @@ __global__ __launch_bounds__(kSeqBlock, 5) void seq_collide_kernel(
 #pragma unroll
       for (int sl = 0; sl < kSeqAhead; ++sl) {
         const int st = st0 + sl;
-        if (st < nsteps) {
-          // every lane reads and writes four words; a lane without a record
-          // in this step uses its spare word for all four
-          const uint2 id = qid[sl];
-          const float4 co = qco[sl];
-          const bool on = qok[sl];
-          const int pa = on ? (int)(id.x & 0xFFFFu) : spare, pb = on ? (int)(id.x >> 16) : spare;
-          const int pas = on ? (int)(id.y & 0xFFFFu) : spare, pbs = on ? (int)(id.y >> 16) : spare;
-          // the four current values, then the four new ones: slots of one
-          // node read the same value and carry the same merged coefficient
-          const float va = tile[pa], vb = tile[pb], vas = tile[pas], vbs = tile[pbs];
-          const float gg = (va + vb) + (epsf * va) * vb;
-          tile[pas] = fmaf(co.x, gg, vas);
-          tile[pbs] = fmaf(co.y, gg, vbs);
-          tile[pa] = fmaf(co.z, gg, va);
-          tile[pb] = fmaf(co.w, gg, vb);
-        }
+        // every lane reads and writes four words; a lane without a record in
+        // this step (past the last one: every lane) uses its spare word for
+        // all four.  No branch: the eight steps are one block, and the
+        // addresses of a step are formed while the previous one's reads are
+        // under way.
+        const uint2 id = qid[sl];
+        const float4 co = qco[sl];
+        const bool on = qok[sl];
+        const int pa = on ? (int)(id.x & 0xFFFFu) : spare, pb = on ? (int)(id.x >> 16) : spare;
+        const int pas = on ? (int)(id.y & 0xFFFFu) : spare, pbs = on ? (int)(id.y >> 16) : spare;
+        // the four current values, then the four new ones: slots of one
+        // node read the same value and carry the same merged coefficient
+        const float va = tile[pa], vb = tile[pb], vas = tile[pas], vbs = tile[pbs];
+        const float gg = (va + vb) + (epsf * va) * vb;
+        tile[pas] = fmaf(co.x, gg, vas);
+        tile[pbs] = fmaf(co.y, gg, vbs);
+        tile[pa] = fmaf(co.z, gg, va);
+        tile[pb] = fmaf(co.w, gg, vb);
         fetch(qd[sl], st + kSeqAhead, sl);
         qd[sl] = dload(st + 2 * kSeqAhead);
       }
     }
   }
+  __builtin_amdgcn_s_setprio(0);
   __syncthreads();
   // ---- S5: M x = r with M_kl = sum w F^c psi_k psi_l and r = eps (moments
   // of h^s - moments of h^c), the moments of h^c being row 0 of the sums
@@ -555,7 +598,7 @@ __global__ __launch_bounds__(kSeqBlock, 5) void seq_collide_kernel(
     Tb.om = const_cast<double*>(vom + ns);
     Tb.xt = xt;
     double acc[20];
-    correction_sums<kSeqBlock>(Tb, P.zmom, tile, tile, n0, n1, n2, acc);
+    correction_sums<kSeqBlock, false>(Tb, P.zmom, tile, tile, n0, n1, n2, acc);
     const int rows = n0 * n1;
     const double t = block_sum20_w0<kSeqBlock>(acc, red, rows >= kSeqBlock ? kSeqBlock / 64 : (rows + 63) / 64);
     if (tid < 64) {
