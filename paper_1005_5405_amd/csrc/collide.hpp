@@ -1996,8 +1996,11 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
       }
     }
   }
+  // the sums of the correction, and the node-by-node store with the defect,
+  // read h^c that other threads formed; the plain vector store without a
+  // correction reads its own thread's
+  if (correct || defect) __syncthreads();
   if (correct) {
-    __syncthreads();
     // (2) FP64 sums of M and r, block-reduced
     double acc[20];
     correction_sums<BLOCK>(T, P.zmom, hs, accf, n0, n1, n2, acc);
