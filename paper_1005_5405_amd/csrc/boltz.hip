@@ -1156,6 +1156,7 @@ static int launch_collide_r(boltz_ctx* c, const float* hs, float* hout, int64_t 
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? BOLTZ_OK : hip_fail(c, e, "seq_collide_kernel launch");
   }
+  if (defect && (flags & BOLTZ_NO_CORRECTION)) flags |= kByNode;
   switch (c->collide_block[table ? 1 : 0]) {
     case 256: launch_collide_b<256>(c, table, hs, hout, s32, flags, defect, st, R); break;
     case 512: launch_collide_b<512>(c, table, hs, hout, s32, flags, defect, st, R); break;

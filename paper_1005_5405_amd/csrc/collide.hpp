@@ -1883,6 +1883,13 @@ __device__ __forceinline__ void collide_body_part(const Params& P, const TablesL
   __syncthreads();
 }
 
+// Set by the host beside the flags of the entry point, where the defect is
+// asked for without the correction: the store then goes node by node and reads
+// h^c without a barrier after the pass that forms it, so both passes take a
+// thread's own nodes.  (A barrier for that case cost the code of the others
+// 2%: 160x160 cells, 6144 pairs, 1342 -> 1365 us a step.)
+constexpr uint32_t kByNode = 2u;
+
 // One cell after its h^s tile is in LDS and the accumulators are cleared
 // (and a barrier passed): S3 + S4 pair pass, h^c, S5 correction, one
 // coalesced store of h^{n+1} to dst.  next() is called once the pair pass is
@@ -1911,8 +1918,9 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
   constexpr int NU = BLOCK == 256 ? 4 : (BLOCK == 512 ? 2 : 1);
   const bool correct = !(flags & 1u);
   // node phases four nodes at a time: rows of whole z quadruples and an
-  // output tile on a 16-byte boundary
-  const bool vec4 = ((n2 & 3) == 0) && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0);
+  // output tile on a 16-byte boundary, and not kByNode
+  const bool vec4 =
+      (((uint32_t)n2 & 3u) | (flags & kByNode)) == 0u && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0);
   const double eps = P.eps;
   // ---- S3 + S4: Jacobi gain/loss, every sample reads the post-stream h
   if (MODE == ACC_SPLIT) {
@@ -1996,11 +2004,8 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
       }
     }
   }
-  // the sums of the correction, and the node-by-node store with the defect,
-  // read h^c that other threads formed; the plain vector store without a
-  // correction reads its own thread's
-  if (correct || defect) __syncthreads();
   if (correct) {
+    __syncthreads();
     // (2) FP64 sums of M and r, block-reduced
     double acc[20];
     correction_sums<BLOCK>(T, P.zmom, hs, accf, n0, n1, n2, acc);
