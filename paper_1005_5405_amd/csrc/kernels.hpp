@@ -219,10 +219,13 @@ __device__ __forceinline__ float xswept_value(const Params& P, const float* h, i
 
 // One workgroup per wall (left, right, top) and per bottom face: the table
 // Phi_w / Phi0 of every node (FP64; only the lid moves, with velocity lid_u
-// along x), then A = sum_out |v_n| w_j and D = sum over the mirror images of
-// the outgoing nodes of |v_n| w R, reduced in one pass with the same tree so
+// along x), A = sum_out |v_n| w_j and D = sum over the mirror images of the
+// outgoing nodes of |v_n| w R, reduced in one pass with the same tree so
 // that a wall at rest (R = 1) gives D = A bitwise.  Launched only when the
-// wall state changes.
+// wall state changes.  One workgroup a wall is bound by latency: a thread
+// forms an outgoing node and its mirror image together, so nothing is read
+// back from the table behind a barrier (200x200 cells, 24^3, moving lid: 6 us
+// less a step; a 64x64, 20^3 context's first step 409 -> 402 us).
 constexpr int kWallConstBlock = 1024;
 
 // Blocks first, first + 1, ... of the full set (0 left, 1 right, 2 top, 3 +
@@ -238,40 +241,40 @@ __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, Wa
   const double tfac = wall == WALL_BOTTOM ? pow(tau, -1.5) : W.tfac[wall];
   double* R = const_cast<double*>(ratio_row(P, wall, pos));
   double s[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const int nax = (wall <= WALL_RIGHT) ? 0 : 1;
+  const int sgn = (wall == WALL_LEFT || wall == WALL_BOTTOM) ? 1 : -1;
+  // the outgoing nodes (vn towards the wall) with their mirror images, and
+  // the nodes at vn = 0: every node once
+#pragma unroll 2
   for (int j = threadIdx.x; j < nv; j += blockDim.x) {
     int jx, jy, jz;
     node_decode(j, n1, n2, jx, jy, jz);
     const double v1 = P.vtab[jx], v2 = P.vtab[kMaxAxis + jy], v3 = P.vtab[2 * kMaxAxis + jz];
-    const double Rj = wall_ratio(v1, v2, v3, Uw, tau, tfac);
-    R[j] = Rj;
-    if (wall == WALL_TOP && v2 < 0.0) {
-      // the lid's part of the shear on it and of its derivatives, which
-      // depend on the walls alone
-      const double w = (P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz];
+    const double vn = sgn * (nax ? v2 : v1);
+    if (vn > 0.0) continue;
+    R[j] = wall_ratio(v1, v2, v3, Uw, tau, tfac);
+    if (vn == 0.0) continue;
+    const int mx = nax ? jx : P.n[0] - 1 - jx, my = nax ? n1 - 1 - jy : jy;
+    const double m1 = P.vtab[mx], m2 = P.vtab[kMaxAxis + my];
+    const double Rm = wall_ratio(m1, m2, v3, Uw, tau, tfac);
+    R[(mx * n1 + my) * n2 + jz] = Rm;
+    const double aw = fabs(vn) * ((P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz]);
+    s[0] += aw;
+    s[1] += aw * Rm;
+    if (wall == WALL_TOP) {
+      // the lid's part of the shear on it and of its derivatives (incoming
+      // nodes, v_y < 0), which depend on the walls alone
+      const double w = (P.omtab[mx] * P.omtab[kMaxAxis + my]) * P.omtab[2 * kMaxAxis + jz];
       double dU, dT;
-      wall_ratio_grad(Rj, v1, v2, v3, Uw, tau, dU, dT);
-      const double c = w * v1 * v2, aw = fabs(v2) * w;
+      wall_ratio_grad(Rm, m1, m2, v3, Uw, tau, dU, dT);
+      const double c = w * m1 * m2, awm = fabs(m2) * w;
       s[2] += c;
-      s[3] += c * Rj;
+      s[3] += c * Rm;
       s[4] += c * dU;
       s[5] += c * dT;
-      s[6] += aw * dU;
-      s[7] += aw * dT;
+      s[6] += awm * dU;
+      s[7] += awm * dT;
     }
-  }
-  __syncthreads();
-  const int nax = (wall <= WALL_RIGHT) ? 0 : 1;
-  const int sgn = (wall == WALL_LEFT || wall == WALL_BOTTOM) ? 1 : -1;
-  for (int j = threadIdx.x; j < nv; j += blockDim.x) {
-    int jx, jy, jz;
-    node_decode(j, n1, n2, jx, jy, jz);
-    const double vn = nax ? P.vtab[kMaxAxis + jy] : P.vtab[jx];
-    if (!(sgn * vn < 0.0)) continue;
-    const double aw = fabs(vn) * ((P.omtab[jx] * P.omtab[kMaxAxis + jy]) * P.omtab[2 * kMaxAxis + jz]);
-    int mx = jx, my = jy;
-    if (nax == 0) mx = P.n[0] - 1 - jx; else my = n1 - 1 - jy;
-    s[0] += aw;
-    s[1] += aw * R[(mx * n1 + my) * n2 + jz];
   }
   if (wall == WALL_TOP) block_sum<8>(s, red);
   else block_sum<2>(reinterpret_cast<double(&)[2]>(s), red);
