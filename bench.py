@@ -348,10 +348,9 @@ def run_adjoint(pkg, torch, preset, steps: int, warmup: int, window: int, every:
                 "collide_adjoint": {"kernel": "collide_adj_kernel + sample_kernel", "avg_ms": t_ca * 1e3,
                                     "bound": "lds", "hbm_bytes_per_node": 20,
                                     "hbm_frac": 20 * nodes / t_ca / 1e9 / HBM_PEAK_GBS},
-                "stream_adjoint": {"kernel": "wall_kernel x2 + wall_adj_kernel x2 + sweep_adj_kernel x2 + "
-                                             "grad_reduce_kernel", "avg_ms": t_sa * 1e3, "bound": "hbm",
-                                   "hbm_bytes_per_node": 32,
-                                   "hbm_frac": 32 * nodes / t_sa / 1e9 / HBM_PEAK_GBS}},
+                "stream_adjoint": {"kernel": "wall_kernel x2 + wall_adj_kernel x2 + stream_adj_kernel",
+                                   "avg_ms": t_sa * 1e3, "bound": "hbm", "hbm_bytes_per_node": 16,
+                                   "hbm_frac": 16 * nodes / t_sa / 1e9 / HBM_PEAK_GBS}},
             "window": {"steps": window, "checkpoint_every": every, "seconds": t_win, "J": J.item(),
                        "gradient_vs_central_differences": fd}}
 
