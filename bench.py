@@ -59,19 +59,19 @@ PAPER_NODE_UPDATES_PER_S = 1.0e9
 # kernels), each scaled by what the counter reads for a device copy of the
 # state (bench.py --calibrate), per workload (cells, velocity grid, G); valid
 # only for the kernel sources whose SHA-256 is recorded (the collide_counters
-# summaries under profiles/).
+# summaries under profiles/, step_kernels_grouped.md for the current ones).
 TRAFFIC = {
-    # sample_kernel + collide_kernel<1024, true, ACC_PART>
-    "200x200_24_G0": {"sha256": "57597daa49de834632e57087beab4a53a322094cd1cfaa93aee33ff37e69ee7d", "fetch_kib": 143.0 + 1085867.5, "fetch_scale": 1.99993,
-                      "write_kib": 1171.88 + 2164097.5, "write_scale": 1.0},
-    # sample_kernel + collide_kernel<1024, true, ACC_FIXED>
-    "64x64_20_G0": {"sha256": "57597daa49de834632e57087beab4a53a322094cd1cfaa93aee33ff37e69ee7d", "fetch_kib": 143.0 + 66042.5, "fetch_scale": 1.99943,
-                    "write_kib": 468.75 + 128000.0, "write_scale": 1.0},
+    # sample_kernel + group_kernel + collide_kernel<1024, true, ACC_PART>
+    "200x200_24_G0": {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "fetch_kib": 1476.1 + 618.4 + 1088089.9, "fetch_scale": 1.99993,
+                      "write_kib": 1171.88 + 1171.88 + 2169216.5, "write_scale": 1.0},
+    # sample_kernel + group_kernel + collide_kernel<1024, true, ACC_FIXED>
+    "64x64_20_G0": {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "fetch_kib": 1050.6 + 254.7 + 66090.0, "fetch_scale": 1.99943,
+                    "write_kib": 468.75 + 468.75 + 128000.0, "write_scale": 1.0},
 }
 # VALU instructions (wave64) per dispatch of the per-cell-sample (G = 1)
 # collision kernel of the 64x64 cavity, rocprofv3 --pmc SQ_INSTS_VALU; valid
 # for the recorded kernel-source SHA-256.
-VALU_G1 = {"sha256": "57597daa49de834632e57087beab4a53a322094cd1cfaa93aee33ff37e69ee7d", "valu_insts_per_dispatch": 4.98797e8}
+VALU_G1 = {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "valu_insts_per_dispatch": 3.43980e8}
 KERNEL_SOURCES = ("adjoint.hpp", "boltz.hip", "collide.hpp", "device_math.hpp", "kernels.hpp", "sequential.hpp")
 
 
@@ -463,7 +463,7 @@ def _roofline(r, kw, g):
     pair_cells = g.ncells * g.n_pairs
     seq = bool(kw.get("flags", 0) & 8)
     kernel = ("sample_kernel + seq_level_kernel + seq_collide_kernel" if seq
-              else "collide_kernel + sample_kernel" if kw["sample_group"] != 1 else "collide_kernel")
+              else "collide_kernel + sample_kernel + group_kernel" if kw["sample_group"] != 1 else "collide_kernel")
     note = ("8 B/node (FP32 h read + write) per launch over the HIP-event average of the collision launch group; "
             "its in-place pair loop (4 LDS reads and 4 LDS writes per record, one level of the shared records "
             "at a time, latency-bound at one wavefront per cell), not HBM, sets its time" if seq else
