@@ -627,7 +627,9 @@ __global__ __launch_bounds__(kSeqBlock, 5) void seq_collide_kernel(
   // defect
   bool finite = true;
   auto out_of = [&](double hc, double xpsi) { return (float)fma(fma(eps, hc, 1.0) * xpsi, P.inv_eps, hc); };
-  if (vec4 && !defect) {
+  if (vec4 && (n2 & 3) == 0 && !defect) {
+    // four nodes of one velocity row (rows of whole quadruples only: one
+    // (v_x, v_y) and four consecutive v_z)
     const f32x4* a4 = reinterpret_cast<const f32x4*>(tile);
     f32x4* d4 = reinterpret_cast<f32x4*>(dst);
     NodeWalk nw4(4 * tid, 4 * kSeqBlock, n1, n2);
