@@ -23,37 +23,30 @@ namespace boltz {
 // dJ/dg = k_a* lI_a* + k_b* lI_b* - k_a lI_a - k_b lI_b and the sample's own
 // coefficients k (FP32 table records or the FP64 values of the draw).
 // AdjFixed: the terms, divided by the cell's power-of-two scale S (inv_s =
-// 1/S), go to 64-bit fixed-point accumulators as in the forward pass; terms
-// of 2^18 S or more take the exact conversion (fixed_exact) up to 2^22 S,
-// and beyond that (or not finite) raise the flag: the cell's sums are then
-// formed again by AdjF64, FP64 compare-and-swap adds.
+// 1/S), go to 64-bit fixed-point accumulators as in the forward pass; a term
+// outside [-win, win) S (or not finite) raises the flag: the cell's sums are
+// then formed again by AdjF64, FP64 compare-and-swap adds.  A record adds at
+// most two terms to one node, so win = min(2^18, 2^30 / N_t) keeps every sum
+// below 2^31 S, the range of the accumulators, however the signs fall.
 struct AdjFixed {
   unsigned long long* acc;
   double inv_s;
   unsigned* flag;
-  static constexpr double kWide = 4194304.0;  // 2^22: 512 such terms at one node stay within 64 bits
-  __device__ __forceinline__ void wide(int j, double k, double f) const {
-    const double x = k * f;
-    unsigned long long v;
-    if (fabs(x) < kWide && fixed_exact(x, v))
-      __hip_atomic_fetch_add(&acc[j], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    else
-      *flag = 1u;
+  unsigned win;
+  __device__ __forceinline__ bool in_range(long long d) const {
+    return (unsigned)((int)(d >> 32)) + win < 2u * win;
   }
   __device__ __forceinline__ void add(int a, int b, double lg, double fa, double fb) const {
     // both values first; straight-line adds when the whole wavefront has
-    // them in the fixed-point window (a discarded sample adds 0)
+    // them in range (a discarded sample adds 0)
     const double ks = lg * inv_s;
     const long long da = fixed_of(ks, fa), db = fixed_of(ks, fb);
-    const bool oa = in_fixed_window(da), ob = in_fixed_window(db);
-    if (__all(oa & ob)) {
+    const bool ok = in_range(da) & in_range(db);
+    if (__all(ok)) {
       __hip_atomic_fetch_add(&acc[a], (unsigned long long)da, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       __hip_atomic_fetch_add(&acc[b], (unsigned long long)db, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    } else {
-      if (oa) __hip_atomic_fetch_add(&acc[a], (unsigned long long)da, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      else wide(a, ks, fa);
-      if (ob) __hip_atomic_fetch_add(&acc[b], (unsigned long long)db, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      else wide(b, ks, fb);
+    } else if (!ok) {
+      *flag = 1u;  // (the other lanes' terms are dropped with the cell's sums)
     }
   }
 };
@@ -467,7 +460,7 @@ __global__ __launch_bounds__(BLOCK, 4) void collide_adj_kernel(Params P, const f
     }
     const int64_t next = cell + gridDim.x;
     if (pvec && next < ncells) pre.load(hs_g + next * nv, tid, BLOCK, nv4);
-    gain_loss_adj<BLOCK, TABLE, 2>(P, T, hs, accf, AdjFixed{acc64, inv_scale, &wide_flag}, group, step, tidx, tcoef);
+    gain_loss_adj<BLOCK, TABLE, 2>(P, T, hs, accf, AdjFixed{acc64, inv_scale, &wide_flag, P.adj_win}, group, step, tidx, tcoef);
     __syncthreads();
     const bool wide = wide_flag != 0u;
     if (wide) {

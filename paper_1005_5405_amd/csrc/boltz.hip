@@ -802,6 +802,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   c->ngroups = ngroups;
   c->records = seq ? kRecordsPlain : record_mode(cmode, ngroups, c->ncells, p->n_pairs, c->nv);
   P.grouped = c->records == kRecordsGroup ? 1 : 0;
+  P.adj_win = (unsigned)std::min<int64_t>((int64_t)1 << 18, ((int64_t)1 << 30) / std::max<int64_t>(1, p->n_pairs));
   c->tidx = ngroups ? reinterpret_cast<uint2*>(base + o_tidx) : nullptr;
   c->tcoef = ngroups ? reinterpret_cast<float4*>(base + o_tcoef) : nullptr;
   c->sidx = nsort ? reinterpret_cast<uint2*>(base + o_sidx) : c->tidx;

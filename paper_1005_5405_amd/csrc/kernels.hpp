@@ -74,6 +74,9 @@ struct Params {
   int continuous;
   // the shared records are rearranged by first node (group_kernel)
   int grouped;
+  // largest term, in units of a cell's scale, of the collide adjoint's
+  // fixed-point sums (AdjFixed)
+  unsigned adj_win;
   // stretched spatial cells (Sec. 5.1; first-order streaming): widths of
   // the x cells and reciprocal widths along x and y, else null
   const double* wx;
