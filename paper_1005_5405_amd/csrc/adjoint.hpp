@@ -972,7 +972,7 @@ __global__ __launch_bounds__(kLidAdjBlock) void lid_adj_kernel(Params P, const f
     publish(&gpart[2 * ix], nwt * (c0 * P.wlid[2]) * P.inv_eps - q * P.wlid[4]);
     publish(&gpart[2 * ix + 1], nwt * (c0 * P.wlid[3]) * P.inv_eps - q * P.wlid[5]);
   }
-  if (last_workgroup(P.count + 1, (uint32_t)P.nx, &flag) && threadIdx.x < 64) {
+  if (last_workgroup(P.count + 2, (uint32_t)P.nx, &flag) && threadIdx.x < 64) {
     const double su = wave_sum_of(gpart, nullptr, P.nx, 2), st = wave_sum_of(gpart + 1, nullptr, P.nx, 2);
     if (threadIdx.x == 0) {
       grad[0] += su;

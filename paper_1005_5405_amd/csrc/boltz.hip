@@ -681,7 +681,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   const size_t o_dpart = off; off = align256(off + (size_t)p->nx * 8);
   const size_t o_wconst = off; off = align256(off + 8 * 8);
   const size_t o_wlid = off; off = align256(off + 6 * 8);
-  const size_t o_count = off; off = align256(off + 2 * 4);
+  const size_t o_count = off; off = align256(off + 3 * 4);
   const size_t o_status = off; off = align256(off + 4);
   const size_t o_lnw = off; off = align256(off + (size_t)nfaces * 8);
   const size_t o_gpart = off; off = align256(off + (size_t)nfaces * 2 * 8);

@@ -60,7 +60,8 @@ struct Params {
   double* wconst_b;       // [nx][2] A, D of every bottom face
   double* wlid;           // [6] sums over the lid's incoming nodes (v_y < 0): w v_x v_y
                           // times 1, R, dR/dU, dR/dtau, then |v_y| w times dR/dU, dR/dtau
-  uint32_t* count;        // [2] finished workgroups (zero between launches)
+  uint32_t* count;        // [3] finished workgroups of the moments', face adjoint's
+                          // and lid adjoint's launches (zero between launches)
   uint32_t* status;       // device status bits
   // ACC_HYBRID collisions: nodes hyb_lo .. hyb_lo + hyb_n - 1 (whole
   // x-slabs) take 64-bit accumulators, the others FP32; hyb_ovf: one row of
@@ -154,15 +155,11 @@ __device__ __forceinline__ void publish(double* p, double v) {
 // Whether this workgroup is the last of `total` to get here (one call each):
 // the values that thread 0 of the others published before are then there to
 // be read (wave_sum_of).  Only atomics of device scope take part: a fence
-// would write back the L2 (10 us a launch).  Leaves the counter at zero.
-// flag: a word of LDS.
+// would write back the L2 (10 us a launch).  The counter wraps to zero after
+// `total` steps, the same total in every launch that uses it, so it is zero
+// again also after launches that ran at the same time.  flag: a word of LDS.
 __device__ __forceinline__ bool last_workgroup(uint32_t* count, uint32_t total, unsigned* flag) {
-  if (threadIdx.x == 0) {
-    const bool last =
-        __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1u;
-    if (last) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *flag = last ? 1u : 0u;
-  }
+  if (threadIdx.x == 0) *flag = atomicInc(count, total - 1u) == total - 1u ? 1u : 0u;
   __syncthreads();
   return *flag != 0u;
 }
