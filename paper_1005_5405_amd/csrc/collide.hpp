@@ -2103,13 +2103,25 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
   __syncthreads();
 }
 
+// Wavefronts per SIMD that the registers must allow: with pairs drawn in the
+// kernel three workgroups of 256 threads (168 registers) or two of 512 (128),
+// with shared records two of 512 in ACC_FIXED.  Elsewhere only what the
+// workgroup needs: a bound that the kernel keeps by itself still costs its code
+// (shared records, 256 threads: 100x100 cells, 8^3, 500 records 75.7 us a
+// collision with the bound, 72.5 without; 48x40, 12^3, 2000: 34.5 and 33.5), and
+// one workgroup of 512 a CU only spills under it (ACC_SPLIT, shared records,
+// 12 100 nodes: 269.6 and 263.2; with drawn pairs 641 and 662).
+constexpr int collide_waves(int block, bool table, int mode) {
+  return table && !(mode == ACC_FIXED && block >= 512) ? 1 : (block == 256 ? 3 : 4);
+}
+
 // Persistent workgroups: workgroup b collides cells b, b + gridDim.x, ...;
 // the h^s tile of the next cell is loaded into registers while the node
 // phases of the current one run.  TABLE: the pairs come from the records of
 // sample_kernel (cells of one group share them).  MODE: accumulation of the
 // increments (ACC_FIXED, ACC_SPLIT, ACC_CAS).  h_s may equal h_out.
 template <int BLOCK, bool TABLE, int MODE, int DRAW = 1>
-__global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 3 : 4) void collide_kernel(Params P, const float* hs_g, float* hout_g, uint32_t step,
+__global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void collide_kernel(Params P, const float* hs_g, float* hout_g, uint32_t step,
                                                         uint32_t flags, double* __restrict__ defect,
                                                         const uint2* __restrict__ tidx,
                                                         const float4* __restrict__ tcoef) {
