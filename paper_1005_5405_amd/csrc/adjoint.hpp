@@ -332,7 +332,7 @@ __global__ __launch_bounds__(BLOCK, 4) void collide_adj_kernel(Params P, const f
     __syncthreads();
     // ---- forward: increments and h^c, and the sums z
     const uint32_t group = (P.sample_group == 0) ? 0u : (uint32_t)(cell / P.sample_group);
-    gain_loss<BLOCK, TABLE, ACC_FIXED, 2, 0, false>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
+    gain_loss<BLOCK, TABLE, ACC_FIXED, 2>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
     __syncthreads();
     double zs[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     auto hc_group = [&](int i, const double (&l)[V]) {

@@ -304,12 +304,19 @@ const void* collide_adj_fn(int block, bool table, bool vec) {
                       : (block == 512 ? collide_adj_fn_b<512>(table, vec) : collide_adj_fn_b<1024>(table, vec));
 }
 
-// table: shared records; else pairs drawn in the kernel by the node law or,
-// with cont, from the continuous Maxwellian
-const void* collide_fn(int block, bool table, int mode, bool cont = false) {
+// Whether the kernel with shared records holds the grouped pair loop (kMayGroup).
+constexpr int record_loops(int block, int mode, bool grouped) {
+  return mode == ACC_FIXED && block != 256 ? kMayGroup
+         : (mode == ACC_FIXED || mode == ACC_PART) && grouped ? kMayGroup : kUngrouped;
+}
+
+// table: shared records (grouped by first node or not); else pairs drawn in
+// the kernel by the node law or, with cont, from the continuous Maxwellian
+const void* collide_fn(int block, bool table, int mode, bool cont, bool grouped) {
 #define BOLTZ_COLLIDE_FN(B, M)                                                                                 \
   if (block == B && mode == M)                                                                                 \
-    return table ? (const void*)collide_kernel<B, true, M>                                                     \
+    return table ? (grouped ? (const void*)collide_kernel<B, true, M, 1, record_loops(B, M, true)>             \
+                            : (const void*)collide_kernel<B, true, M, 1, record_loops(B, M, false)>)           \
                  : (cont ? (const void*)collide_kernel<B, false, M, 2> : (const void*)collide_kernel<B, false, M, 1>);
   BOLTZ_COLLIDE_FN(256, ACC_FIXED)
   BOLTZ_COLLIDE_FN(512, ACC_FIXED)
@@ -842,7 +849,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   for (int t = 0; t < 2 && ea == hipSuccess && !seq; ++t) {
     if (cmode == ACC_FIXED && !std::getenv("BOLTZ_COLLIDE_BLOCK"))
       c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, P.continuous != 0, c->ncells, ncu < 1 ? 1 : ncu);
-    const void* fn = collide_fn(cblock[t], t == 1, cmode, (p->flags & BOLTZ_CONTINUOUS_PAIRS) != 0);
+    const void* fn = collide_fn(cblock[t], t == 1, cmode, P.continuous != 0, P.grouped != 0);
     c->collide_lds[t] = cmode == ACC_HYBRID ? CollideLDS::hyb_bytes(c->nv, hn[t], nsum, t == 0)
                         : cmode == ACC_PART ? CollideLDS::part_bytes(c->nv, hn[t], nsum, t == 0)
                                             : CollideLDS::bytes(c->nv, nsum, cmode, t == 0);
@@ -1079,9 +1086,12 @@ static void launch_collide_m(boltz_ctx* c, bool table, const float* hs, float* h
   Params P = c->P;
   P.hyb_lo = c->hyb_lo[t];
   P.hyb_n = c->hyb_n[t];
-  if (table)
-    hipLaunchKernelGGL((collide_kernel<B, true, M>), grid, dim3(B), lds, st, P, hs, hout, s32, flags, defect,
-                       R.tidx, R.tcoef);
+  if (table && P.grouped)
+    hipLaunchKernelGGL((collide_kernel<B, true, M, 1, record_loops(B, M, true)>), grid, dim3(B), lds, st, P, hs, hout,
+                       s32, flags, defect, R.tidx, R.tcoef);
+  else if (table)
+    hipLaunchKernelGGL((collide_kernel<B, true, M, 1, record_loops(B, M, false)>), grid, dim3(B), lds, st, P, hs, hout,
+                       s32, flags, defect, R.tidx, R.tcoef);
   else if (P.continuous)
     hipLaunchKernelGGL((collide_kernel<B, false, M, 2>), grid, dim3(B), lds, st, P, hs, hout, s32, flags, defect,
                        R.tidx, R.tcoef);
@@ -1329,9 +1339,7 @@ static void launch_collide_adj_b(boltz_ctx* c, bool table, const float* hs, cons
                                  uint32_t s32, uint32_t flags, hipStream_t st) {
   const int t = table ? 1 : 0;
   auto go = [&](auto kern) {
-    Params P = c->P;
-    P.grouped = 0;
-    hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, P, hs, lo, ls, s32,
+    hipLaunchKernelGGL(kern, dim3((unsigned)c->adj_grid[t]), dim3(B), c->adj_lds[t], st, c->P, hs, lo, ls, s32,
                        flags, c->tidx, c->tcoef);
   };
   // four nodes per access: whole quadruples per row, 16-byte aligned buffers

@@ -1014,13 +1014,6 @@ __device__ __forceinline__ void lds_add64(unsigned long long* p, long long d) {
   __hip_atomic_fetch_add(p, (unsigned long long)d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// S3 + S4 for one cell (Eqs. monteCarloInt, collision_step in Jacobi form):
-// every sample reads the post-stream tile hs and adds its gain and loss to
-// the accumulators.  TABLE: the pairs are the records of sample_kernel for
-// the cell's group, four per thread and pass so that their loads and
-// gathers are in flight together; else they are drawn here.
-// DRAW (pairs drawn here, not TABLE): 1 the node law, 2 continuous pairs,
-// 0 whichever the problem asks for (chosen once, outside the loop).
 // Walk of a table of nt records by BLOCK threads, PU per thread and pass:
 // pass(first record, distance, masked).  chunked: in chunks of 256 records per
 // wavefront, record u of a lane 64 u further (the order of group_kernel);
@@ -1042,8 +1035,23 @@ __device__ __forceinline__ void table_walk(uint32_t nt, int tid, bool chunked, P
   if (m < nt) pass(m, BLOCK, true);
 }
 
-// GROUP: the records may be grouped by first node (group_kernel).
-template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0, bool GROUP = MODE == ACC_FIXED>
+// Whether the shared records may be grouped by first node (group_kernel); the
+// problem tells.  Records that are not have an instance without the grouped
+// loop, which costs registers and code, in ACC_PART (32x32 cells, 24^3, 20 000
+// records in order: 99.8 us a collision with both loops, 94.7 without) and
+// with 256 threads (50x50, 13x11x9, 3001 records: 48.2 and 47.8 us).  The other
+// ACC_FIXED kernels hold both (64x64, 20^3, grouped: 341.8 us a step with
+// both, 344.5 with an instance each; 64x64, 16^3, dealt: 160.5 and 162.4).
+enum : int { kUngrouped = 0, kMayGroup = 1 };
+
+// S3 + S4 for one cell (Eqs. monteCarloInt, collision_step in Jacobi form):
+// every sample reads the post-stream tile hs and adds its gain and loss to
+// the accumulators.  TABLE: the pairs are the records of sample_kernel for
+// the cell's group, four per thread and pass so that their loads and
+// gathers are in flight together; else they are drawn here.
+// DRAW (pairs drawn here, not TABLE): 1 the node law, 2 continuous pairs,
+// 0 whichever the problem asks for (chosen once, outside the loop).
+template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0, int GR = kUngrouped>
 __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, const float* hs, float* accf,
                                           unsigned long long* acc64, uint32_t group, uint32_t step,
                                           const uint2* __restrict__ tidx, const float4* __restrict__ tcoef,
@@ -1068,7 +1076,7 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
         id[u] = ok[u] ? ri[mu] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[mu] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      if (GROUP && !masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
+      if (GR != kUngrouped && !masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
         // the PU records of a lane share their first node: one gather and
         // one add there
         const int a = (int)(id[0].x & kNodeMask);
@@ -1131,7 +1139,7 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
         }
       }
     };
-    table_walk<BLOCK, PU>(nt, tid, GROUP && P.grouped, pass);
+    table_walk<BLOCK, PU>(nt, tid, GR == kMayGroup && P.grouped, pass);
   } else {
     auto draw = [&](auto&& sampler) {
       for (uint32_t m = tid; m < nt; m += BLOCK) {
@@ -1156,7 +1164,7 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
 // memory (a load for the few lanes that need it, issued after every LDS
 // gather of the pass).  BLOCK threads take part, tid = 0 .. BLOCK - 1 (a
 // multiple of 64, so shared record m stays with lane m mod 64).
-template <int BLOCK, bool TABLE, int PU = 4, int DRAW = 0>
+template <int BLOCK, bool TABLE, int PU = 4, int DRAW = 0, int GR = kUngrouped>
 __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS& T, const Part& Q, uint32_t group,
                                                uint32_t step, const uint2* __restrict__ tidx,
                                                const float4* __restrict__ tcoef, int tid) {
@@ -1176,7 +1184,7 @@ __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS&
         id[u] = ok[u] ? ri[mu] : make_uint2(0u, 0u);
         kk[u] = ok[u] ? rk[mu] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      if (!masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
+      if (GR != kUngrouped && !masked && (__builtin_amdgcn_readfirstlane(id[0].x) & kGroupFlag)) {
         // the PU records of a lane share their first node
         const int a = (int)(id[0].x & kNodeMask);
         const bool ia = Q.inner(a);
@@ -1241,7 +1249,7 @@ __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS&
                        (int)(id[u].y >> 16), kk[u].x, kk[u].y, kk[u].z, kk[u].w, g);
       }
     };
-    table_walk<BLOCK, PU>(nt, tid, P.grouped, pass);
+    table_walk<BLOCK, PU>(nt, tid, GR == kMayGroup && P.grouped, pass);
   } else {
     auto draw = [&](auto&& sampler) {
       for (uint32_t m = tid; m < nt; m += BLOCK) {
@@ -1750,7 +1758,7 @@ __device__ __forceinline__ int correction_sums_part(const TablesLDS& T, const do
 // One cell in the ACC_PART layout (inner h^s tile in LDS, Q.hg the cell's
 // row, accumulators cleared, a barrier passed): as collide_body_hybrid.
 // vec: rows of whole z quadruples and a 16-byte aligned global row.
-template <int BLOCK, bool TABLE, class Next, int PU = 4, int DRAW = 0>
+template <int BLOCK, bool TABLE, class Next, int PU = 4, int DRAW = 0, int GR = kUngrouped>
 __device__ __forceinline__ void collide_body_part(const Params& P, const TablesLDS& T, const Part& Q, double* red,
                                                   bool vec, uint32_t group, uint32_t step, uint32_t flags,
                                                   float* dst, double* defect, const uint2* __restrict__ tidx,
@@ -1760,7 +1768,7 @@ __device__ __forceinline__ void collide_body_part(const Params& P, const TablesL
   const bool correct = !(flags & 1u);
   const bool vec4 = vec && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0);
   const double eps = P.eps;
-  gain_loss_part<BLOCK, TABLE, PU, DRAW>(P, T, Q, group, step, tidx, tcoef, tid);
+  gain_loss_part<BLOCK, TABLE, PU, DRAW, GR>(P, T, Q, group, step, tidx, tcoef, tid);
   __syncthreads();
   next();
   const bool flagged = *Q.flag != 0u;
@@ -1899,7 +1907,7 @@ constexpr uint32_t kByNode = 2u;
 // accumulators (the persistent kernel stages the next cell there); defect:
 // the cell's five values or null.  Ends with a barrier, so the LDS can be
 // refilled.
-template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0, class Next, class Early>
+template <int BLOCK, bool TABLE, int MODE, int PU = 4, int DRAW = 0, int GR = kUngrouped, class Next, class Early>
 __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T, float* hs, float* accf,
                                              unsigned long long* acc64, double* red, uint32_t group,
                                              uint32_t step, uint32_t flags, float* dst, double* defect,
@@ -1960,7 +1968,7 @@ __device__ __forceinline__ void collide_body(const Params& P, const TablesLDS& T
     }
     __syncthreads();
   } else {
-    gain_loss<BLOCK, TABLE, MODE, PU, DRAW>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
+    gain_loss<BLOCK, TABLE, MODE, PU, DRAW, GR>(P, T, hs, accf, acc64, group, step, tidx, tcoef);
     __syncthreads();
     next();
     // ---- S5 (1): h^c = h^s + increment, stored over the FP32 accumulator;
@@ -2120,7 +2128,7 @@ constexpr int collide_waves(int block, bool table, int mode) {
 // phases of the current one run.  TABLE: the pairs come from the records of
 // sample_kernel (cells of one group share them).  MODE: accumulation of the
 // increments (ACC_FIXED, ACC_SPLIT, ACC_CAS).  h_s may equal h_out.
-template <int BLOCK, bool TABLE, int MODE, int DRAW = 1>
+template <int BLOCK, bool TABLE, int MODE, int DRAW = 1, int GR = kUngrouped>
 __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void collide_kernel(Params P, const float* hs_g, float* hout_g, uint32_t step,
                                                         uint32_t flags, double* __restrict__ defect,
                                                         const uint2* __restrict__ tidx,
@@ -2221,7 +2229,7 @@ __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void coll
       auto next_part = [&]() {
         if (pvec && next < ncells) pre.load(hs_g + next * nv + Q.lo, tid, BLOCK, nin4);
       };
-      collide_body_part<BLOCK, TABLE, decltype(next_part)&, 4, DRAW>(
+      collide_body_part<BLOCK, TABLE, decltype(next_part)&, 4, DRAW, GR>(
           P, T, Q, red, vec, group, step, flags, hout_g + cell * nv, defect ? defect + cell * 5 : nullptr, tidx,
           tcoef, next_part);
     }
@@ -2275,7 +2283,7 @@ __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void coll
     // vector-memory waits retire in issue order, so loads issued before the
     // pair loop would stall its first record loads; the node phases wait on
     // no vector load.
-    collide_body<BLOCK, TABLE, MODE, 4, DRAW>(
+    collide_body<BLOCK, TABLE, MODE, 4, DRAW, GR>(
         P, T, hs, accf, acc64, red, group, step, flags, hout_g + cell * nv, defect ? defect + cell * 5 : nullptr,
         tidx, tcoef,
         [&]() {
@@ -2355,7 +2363,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 3 : 4) void collide_batch_ker
         float* dst = hout + C.hoff + cell * nv;
         auto none = []() {};
         if (table)
-          collide_body_part<BLOCK, true, decltype(none)&, PU>(P, T, Q, red, vec, group, step, 0u, dst, nullptr, C.tidx,
+          collide_body_part<BLOCK, true, decltype(none)&, PU, 0, kMayGroup>(P, T, Q, red, vec, group, step, 0u, dst, nullptr, C.tidx,
                                                              C.tcoef, none);
         else
           collide_body_part<BLOCK, false, decltype(none)&, PU>(P, T, Q, red, vec, group, step, 0u, dst, nullptr,
@@ -2390,7 +2398,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 256 ? 3 : 4) void collide_batch_ker
     float* dst = hout + C.hoff + cell * nv;
     auto none = []() {};
 #define BOLTZ_BODY(TB, MD)                                                                                      \
-  collide_body<BLOCK, TB, MD, PU>(P, T, hs, accf, acc64, red, group, step, 0u, dst, nullptr, C.tidx, C.tcoef, none, \
+  collide_body<BLOCK, TB, MD, PU, 0, MD == ACC_FIXED ? kMayGroup : kUngrouped>(P, T, hs, accf, acc64, red, group, step, 0u, dst, nullptr, C.tidx, C.tcoef, none, \
                                   none)
     if (table) {
       if (mode == ACC_FIXED) BOLTZ_BODY(true, ACC_FIXED);
