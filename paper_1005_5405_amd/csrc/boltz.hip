@@ -254,22 +254,32 @@ bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
   return true;
 }
 
-// Threads per workgroup of the ACC_FIXED collide kernel: one workgroup of 1024
-// where the LDS or the number of cells gives a CU one cell at a time (64x64,
-// 20^3: 280 us a launch against 311 with 512; 16x16, 12^3, own pairs: step
-// 36.7 us against 37.6), two of 512 where two cells fit (32x24, 16^3, 8000
-// shared pairs: 34 us against 41 with one of 1024), three of 256 beyond (33x21,
-// 13x11x9, 3001 pairs: 20.5 us against 24.8 with 512).  128 registers a thread
-// at 1024 and 512 threads, 168 at 256.
-// Continuous pairs drawn in the kernel need every wavefront the registers
-// allow: two of 512 there (25x67, 8x21x7, 6246 own pairs: 364 us a step
-// against 456 with three of 256).
-int collide_block(int nv, int ns, bool sampler, bool continuous, int64_t ncells, int ncu) {
+// Threads per workgroup of the ACC_FIXED collide kernel (us a collision; cells a
+// CU: the most that one gets; 128 registers a thread at 1024 and 512 threads,
+// up to 168 at 256):
+//   one workgroup of 1024 where the LDS or the number of cells gives a CU one
+//   cell at a time (64x64, 20^3: 280 against 311 with 512; 16x16, 12^3, 3000
+//   own pairs 16.0 against 23.2 with 256);
+//   three of 256 where they fit and a CU gets three cells (33x21, 13x11x9, 3001
+//   shared records: 20.5 against 24.8 with 512), with shared records two (576
+//   cells, 14^3, 8000: 31.4 against 33.5; 8^3, 300: 12.8 against 15.1);
+//   two of 512 between (32x24, 16^3, 8000 records: 34 against 41 with 1024; 576
+//   cells, 16^3, 8000: 36.4 against 37.7 with two of 256).
+// A light pair loop does not fill more than 256 threads: fewer than two records a
+// thread (16x16 cells, 8^3, 300 records: 12.1 against 13.0 with 1024, even at
+// 1000), with drawn pairs fewer than three draws a thread where a CU has two
+// cells (32x32, 8^3, 300 continuous pairs 28.6 against 31.4 with 512, 1000
+// pairs 49.0 against 52.1, 64x64 82.7 against 101 and 188 against 183).
+// Continuous pairs beyond that need every wavefront the registers allow: two
+// of 512 (25x67, 8x21x7, 6246 own pairs: 364 a step against 456 with three of
+// 256; 64x64, 12^3, 3000: 460 against 507).
+int collide_block(int nv, int ns, bool sampler, bool continuous, int64_t n_pairs, int64_t ncells, int ncu) {
   const int64_t cells = (ncells + ncu - 1) / ncu;
   auto fit = [&](int block) {
     return (int64_t)(kLdsBytes / (CollideLDS::bytes(nv, ns, ACC_FIXED, sampler) + collide_static_lds(block)));
   };
-  if (cells >= 3 && fit(256) >= 3 && !(sampler && continuous)) return 256;
+  if (sampler ? n_pairs < 768 && cells >= 2 && fit(256) >= 2 : n_pairs < 512 && fit(256) >= 2) return 256;
+  if (cells >= (sampler ? 3 : 2) && fit(256) >= 3 && !(sampler && continuous)) return 256;
   if (cells >= 2 && fit(512) >= 2) return 512;
   return 1024;
 }
@@ -848,7 +858,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   }
   for (int t = 0; t < 2 && ea == hipSuccess && !seq; ++t) {
     if (cmode == ACC_FIXED && !std::getenv("BOLTZ_COLLIDE_BLOCK"))
-      c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, P.continuous != 0, c->ncells, ncu < 1 ? 1 : ncu);
+      c->collide_block[t] = cblock[t] = collide_block(c->nv, nsum, t == 0, P.continuous != 0, p->n_pairs, c->ncells, ncu < 1 ? 1 : ncu);
     const void* fn = collide_fn(cblock[t], t == 1, cmode, P.continuous != 0, P.grouped != 0);
     c->collide_lds[t] = cmode == ACC_HYBRID ? CollideLDS::hyb_bytes(c->nv, hn[t], nsum, t == 0)
                         : cmode == ACC_PART ? CollideLDS::part_bytes(c->nv, hn[t], nsum, t == 0)
