@@ -11,13 +11,14 @@ namespace boltz {
 // ---------------------------------------------------------------- tables --
 // LDS copies of the per-axis tables, ns = n0 + n1 + n2 entries each:
 //   v, om, xt        always (moment sums and the correction)
-//   icdf, edge       only where pairs are drawn
+//   rw, edge, icdf   only where pairs are drawn (rw: continuous ones)
 struct TablesLDS {
   double* v;      // node velocities
   double* om;     // omega, FP64
   double* xt;     // per-axis parts of x . psi of the correction (per cell)
   double* m0;     // [16] sum_j w_j psi_k psi_l (packed k <= l), constant
   uint8_t* icdf;  // [3 * kFieldSize] Maxwellian inverse CDF on 12-bit fields
+  double* rw;     // 1 / omega per axis (continuous pairs)
   double* edge;   // [ns + 3] cell edges per axis (n + 1 each), for the search
                   // of post-collision cells on stretched grids
 
@@ -37,13 +38,15 @@ __device__ __forceinline__ void load_tables(const Params& P, unsigned char* base
   T.om = T.v + ns;
   T.xt = T.om + ns;
   T.m0 = T.xt + ns;
-  T.edge = T.m0 + 16;
+  T.rw = T.m0 + 16;
+  T.edge = T.rw + ns;
   T.icdf = reinterpret_cast<uint8_t*>(T.edge + ns + 3);
   for (int i = threadIdx.x; i < ns; i += blockDim.x) {
     const int k = i < n0 ? 0 : (i < n0 + n1 ? 1 : 2);
     const int o = k * kMaxAxis + i - (k == 0 ? 0 : (k == 1 ? n0 : n0 + n1));
     T.v[i] = P.vtab[o];
     T.om[i] = P.omtab[o];
+    if (sampler && P.continuous) T.rw[i] = 1.0 / P.omtab[o];
   }
   if (sampler) {
     // n + 1 edges per axis, axis k at offset n0 + ... + n_{k-1} + k
@@ -291,10 +294,14 @@ __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const Ta
     p.as = node_index(sx, sy, sz, n1, n2);
     p.bs = node_index(tx, ty, tz, n1, n2);
     p.q = P.qfac * fabs(alpha);
-    p.ka = p.q * P.rwnode[p.a];
-    p.kb = p.q * P.rwnode[p.b];
-    p.kas = p.q * P.rwnode[p.as];
-    p.kbs = p.q * P.rwnode[p.bs];
+    // 1 / w of the four nodes from the axes' factors in LDS (as the per-node
+    // table has it): the FP64 geometry leaves the LDS idle, and four gathers
+    // from memory wait for their latency (64x64 cells, 8^3, 3000 own pairs
+    // 450 us a collision with the gathers, 404 so; 20^3, 20 000: 2619, 2523)
+    p.ka = p.q * ((T.rw[ax] * T.rw[n0 + ay]) * T.rw[n0 + n1 + az]);
+    p.kb = p.q * ((T.rw[bx] * T.rw[n0 + by]) * T.rw[n0 + n1 + bz]);
+    p.kas = p.q * ((T.rw[sx] * T.rw[n0 + sy]) * T.rw[n0 + n1 + sz]);
+    p.kbs = p.q * ((T.rw[tx] * T.rw[n0 + ty]) * T.rw[n0 + n1 + tz]);
   } else {
     p.as = -1;
     p.bs = -1;
