@@ -11,7 +11,8 @@ namespace boltz {
 // ---------------------------------------------------------------- tables --
 // LDS copies of the per-axis tables, ns = n0 + n1 + n2 entries each:
 //   v, om, xt        always (moment sums and the correction)
-//   rw, edge, icdf   only where pairs are drawn (rw: continuous ones)
+//   edge, icdf       only where pairs are drawn
+//   rw               only where a collide kernel draws continuous pairs
 struct TablesLDS {
   double* v;      // node velocities
   double* om;     // omega, FP64
@@ -24,14 +25,16 @@ struct TablesLDS {
 
   static __host__ __device__ size_t bytes(int ns, bool sampler) {
     size_t b = 24 * (size_t)ns + 16 * sizeof(double);
-    // (the layouts' limits were set with 32 bytes per entry here; the tables
-    // now take 8 of them)
+    // (32 bytes an entry, of which the tables take 16: which grids each layout
+    // takes, and which are refused, stays as it was with four tables)
     if (sampler) b += 32 * (size_t)ns + 24 + 3 * (size_t)kFieldSize;
     return b;
   }
 };
 
 // base: 16-byte aligned LDS.  The caller synchronises before use.
+// RW: with rw (else it holds nothing).
+template <bool RW = false>
 __device__ __forceinline__ void load_tables(const Params& P, unsigned char* base, bool sampler, TablesLDS& T) {
   const int n0 = P.n[0], n1 = P.n[1], n2 = P.n[2], ns = n0 + n1 + n2;
   T.v = reinterpret_cast<double*>(base);
@@ -46,7 +49,7 @@ __device__ __forceinline__ void load_tables(const Params& P, unsigned char* base
     const int o = k * kMaxAxis + i - (k == 0 ? 0 : (k == 1 ? n0 : n0 + n1));
     T.v[i] = P.vtab[o];
     T.om[i] = P.omtab[o];
-    if (sampler && P.continuous) T.rw[i] = 1.0 / P.omtab[o];
+    if (RW) T.rw[i] = 1.0 / P.omtab[o];
   }
   if (sampler) {
     // n + 1 edges per axis, axis k at offset n0 + ... + n_{k-1} + k
@@ -130,6 +133,7 @@ struct Pair {
 // is below mix16; k_z = 2 (r3 + 1/2) 2^-32 - 1, azimuth 2 pi (phi + 1/2) 2^-16;
 // v* = v_a + (v_r.k) k, v1* = v_b - (v_r.k) k with v_r = v_b - v_a;
 // post-collision cells floor((x + a) n / 2a), discard outside the box.
+template <bool RW>
 __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const TablesLDS& T, uint32_t group,
                                                        uint32_t step, uint32_t m, u32x4* words);
 
@@ -250,6 +254,7 @@ __device__ __forceinline__ int velocity_cell(const Params& P, const TablesLDS& T
 // Weight q = dt K |v_r . k| / N_t (Phi0 is the sampling density); a pair
 // with any velocity outside the box is discarded, a and b then -1 when v or
 // v1 is outside.  words: block A.
+template <bool RW>
 __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const TablesLDS& T, uint32_t group,
                                                        uint32_t step, uint32_t m, u32x4* words) {
   const int n0 = P.n[0], n1 = P.n[1], n2 = P.n[2];
@@ -294,14 +299,24 @@ __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const Ta
     p.as = node_index(sx, sy, sz, n1, n2);
     p.bs = node_index(tx, ty, tz, n1, n2);
     p.q = P.qfac * fabs(alpha);
-    // 1 / w of the four nodes from the axes' factors in LDS (as the per-node
-    // table has it): the FP64 geometry leaves the LDS idle, and four gathers
-    // from memory wait for their latency (64x64 cells, 8^3, 3000 own pairs
-    // 450 us a collision with the gathers, 404 so; 20^3, 20 000: 2619, 2523)
-    p.ka = p.q * ((T.rw[ax] * T.rw[n0 + ay]) * T.rw[n0 + n1 + az]);
-    p.kb = p.q * ((T.rw[bx] * T.rw[n0 + by]) * T.rw[n0 + n1 + bz]);
-    p.kas = p.q * ((T.rw[sx] * T.rw[n0 + sy]) * T.rw[n0 + n1 + sz]);
-    p.kbs = p.q * ((T.rw[tx] * T.rw[n0 + ty]) * T.rw[n0 + n1 + tz]);
+    if (RW) {
+      // 1 / w of the four nodes from the axes' factors in LDS (as the per-node
+      // table has it): in a collide kernel the FP64 geometry leaves the LDS
+      // idle, and gathers from memory wait for their latency (64x64 cells, 8^3,
+      // 3000 own pairs 450 us a collision with the gathers, 401 so; 20^3, 20 000:
+      // 2619, 2519).  Not for shared records: loading the factors costs more than
+      // a workgroup's 1024 draws gain (64x64, 20^3, groups of four cells 627 us,
+      // 657 with them).
+      p.ka = p.q * ((T.rw[ax] * T.rw[n0 + ay]) * T.rw[n0 + n1 + az]);
+      p.kb = p.q * ((T.rw[bx] * T.rw[n0 + by]) * T.rw[n0 + n1 + bz]);
+      p.kas = p.q * ((T.rw[sx] * T.rw[n0 + sy]) * T.rw[n0 + n1 + sz]);
+      p.kbs = p.q * ((T.rw[tx] * T.rw[n0 + ty]) * T.rw[n0 + n1 + tz]);
+    } else {
+      p.ka = p.q * P.rwnode[p.a];
+      p.kb = p.q * P.rwnode[p.b];
+      p.kas = p.q * P.rwnode[p.as];
+      p.kbs = p.q * P.rwnode[p.bs];
+    }
   } else {
     p.as = -1;
     p.bs = -1;
@@ -316,7 +331,7 @@ __device__ __forceinline__ Pair sample_pair_continuous(const Params& P, const Ta
 // compiled with one sampler's registers).
 __device__ __forceinline__ Pair sample_pair(const Params& P, const TablesLDS& T, uint32_t group, uint32_t step,
                                             uint32_t m, u32x4* words) {
-  return P.continuous ? sample_pair_continuous(P, T, group, step, m, words)
+  return P.continuous ? sample_pair_continuous<false>(P, T, group, step, m, words)
                       : sample_pair_node(P, T, group, step, m, words);
 }
 
@@ -1160,8 +1175,8 @@ __device__ __forceinline__ void gain_loss(const Params& P, const TablesLDS& T, c
       }
     };
     if constexpr (DRAW == 1) draw(sample_pair_node);
-    else if constexpr (DRAW == 2) draw(sample_pair_continuous);
-    else if (P.continuous) draw(sample_pair_continuous);
+    else if constexpr (DRAW == 2) draw(sample_pair_continuous<true>);
+    else if (P.continuous) draw(sample_pair_continuous<false>);
     else draw(sample_pair_node);
   }
 }
@@ -1270,8 +1285,8 @@ __device__ __forceinline__ void gain_loss_part(const Params& P, const TablesLDS&
       }
     };
     if constexpr (DRAW == 1) draw(sample_pair_node);
-    else if constexpr (DRAW == 2) draw(sample_pair_continuous);
-    else if (P.continuous) draw(sample_pair_continuous);
+    else if constexpr (DRAW == 2) draw(sample_pair_continuous<true>);
+    else if (P.continuous) draw(sample_pair_continuous<false>);
     else draw(sample_pair_node);
   }
 }
@@ -2160,7 +2175,7 @@ __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void coll
     H.n = (unsigned)nin;
     H.ovf = P.hyb_ovf + (int64_t)blockIdx.x * nv;
     TablesLDS T;
-    load_tables(P, dsm + CollideLDS::tile(nv) + CollideLDS::hyb_acc(nv, nin), !TABLE, T);
+    load_tables<!TABLE && DRAW == 2>(P, dsm + CollideLDS::tile(nv) + CollideLDS::hyb_acc(nv, nin), !TABLE, T);
     {
       uint4* z = reinterpret_cast<uint4*>(dsm + CollideLDS::tile(nv));
       const int nz = (int)(CollideLDS::hyb_acc(nv, nin) / 16);
@@ -2204,7 +2219,7 @@ __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void coll
     Q.n = (unsigned)nin;
     Q.ovf = P.hyb_ovf + (int64_t)blockIdx.x * nv;
     TablesLDS T;
-    load_tables(P, dsm + CollideLDS::part64(nv) + CollideLDS::tile(nin), !TABLE, T);
+    load_tables<!TABLE && DRAW == 2>(P, dsm + CollideLDS::part64(nv) + CollideLDS::tile(nin), !TABLE, T);
     {
       uint4* z = reinterpret_cast<uint4*>(dsm);
       const int nz = (int)(CollideLDS::part64(nv) / 16);
@@ -2246,7 +2261,7 @@ __global__ __launch_bounds__(BLOCK, collide_waves(BLOCK, TABLE, MODE)) void coll
   unsigned long long* acc64 =
       reinterpret_cast<unsigned long long*>(dsm + (MODE == ACC_SPLIT ? 1 : 2) * CollideLDS::tile(nv));
   TablesLDS T;
-  load_tables(P, dsm + CollideLDS::tile(nv) + CollideLDS::acc(nv, MODE), !TABLE, T);
+  load_tables<!TABLE && DRAW == 2>(P, dsm + CollideLDS::tile(nv) + CollideLDS::acc(nv, MODE), !TABLE, T);
   const int nv4 = nv >> 2;
   constexpr int NR = prefetch_regs<BLOCK>();
   const bool vec = ((nv & 3) == 0) && nv4 <= NR * BLOCK && ((reinterpret_cast<uintptr_t>(hs_g) & 15) == 0);
