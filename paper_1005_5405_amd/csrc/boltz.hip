@@ -54,7 +54,8 @@ struct boltz_ctx {
   size_t collide_lds[2] = {0, 0};
   int64_t collide_grid[2] = {0, 0};
   int64_t ngroups = 0;          // sample groups (shared-sample mode)
-  int records = kRecordsPlain;  // what becomes of the drawn records
+  int records = kRecordsPlain;  // what becomes of the drawn records ...
+  int face_records = kRecordsPlain;  // ... and of those drawn with the y faces
   // wall state the ratio tables Phi_w / Phi0 were last built for
   WallArgs ratio_walls{};
   std::vector<double> ratio_taub;   // bottom-face temperatures of that state
@@ -208,24 +209,40 @@ bool pick_part(const int (&n)[3], int ns, bool sampler, int& lo, int& nin) {
   return false;
 }
 
+// Whether one workgroup of the collision has a CU's LDS to itself.
+bool tile_fills_cu(int mode, int nv, int ns) {
+  return mode != ACC_FIXED ||
+         2 * (CollideLDS::bytes(nv, ns, ACC_FIXED, false) + collide_static_lds(512)) > kLdsBytes;
+}
+
 // What becomes of the shared records between the sampler and the collision
-// (a table of nt records for each of ngroups sample groups):
-//   grouped by first node (group_kernel, 8 us, less where the y faces hide it)
-//   where the pair loops it shortens are long: 64x64 cells, 20^3, 20 000 pairs
-//   (8e7 record-cells) save 12 us a collision, so from 6e7 record-cells on,
-//   and 512 cells a group;
-//   else dealt to lanes (about 4 us of the sampler's latency for 4% of the
-//   pair loop): from 3e7 record-cells and 128 cells a group;
-//   else left in order (33x21 cells, 13x11x9 nodes, 3001 pairs, four cells a
-//   group: sampler launch 34 us dealt, 18 us in order).
-int record_mode(int mode, int64_t ngroups, int64_t ncells, int64_t nt, int nv) {
+// (a table of nt records for each of ngroups sample groups; faces: drawn in the
+// launch of the y faces, which hides part of it).  Times in us, in order /
+// dealt / grouped, G = 0:
+//   grouped by first node (group_kernel) where the pair loops it shortens are
+//   long: from 2.5e7 record-cells in ACC_FIXED (a collision: 20^3, 20 000
+//   records, 32x32 cells 77.9 / 79.4 / 80.0, 48x48 161.6 / 158.1 / 155.3; 6144
+//   records, 64x64 170.1 / 170.3 / 165.1; 12^3, 2100, 128x128 205.7 / 210.7 /
+//   201.9) and 6e7 in ACC_PART (24^3, 20 000: 48x48 199.8 / 202.9 / 204.4, 64x64
+//   345.4 / 345.7 / 343.5), from 512 cells a group (64x64, 20^3: 7% of a step with
+//   one group, 3% with 64 cells a group) and 2048 records (24^3, 2100 records,
+//   160x160: 1137 / 1143 / 1158; 20^3 800 / 794 / 787);
+//   else dealt to lanes where one workgroup has the CU's LDS (smaller tiles, two or
+//   more workgroups a CU, lose at any size: 16^3, 64x64, 8000 records 155.8 /
+//   160.1): from 3e7 record-cells and 128 cells a group (64x64, 20^3, 64 cells a
+//   group 373 / 383 a step), and with the faces from 1e7 (a step of 20^3, 20 000
+//   records: 16x16 cells 51.4 / 51.1, 24x24 95.2 / 93.8, 32x32 111.6 / 109.5; 24^3,
+//   32x32 144.8 / 143.9);
+//   else left in order.
+int record_mode(int mode, int64_t ngroups, int64_t ncells, int64_t nt, int nv, int ns, bool faces) {
   if (ngroups < 1 || (mode != ACC_FIXED && mode != ACC_PART && mode != ACC_HYBRID && mode != ACC_CAS))
     return kRecordsPlain;
   const double work = (double)ncells * (double)nt;
-  if ((mode == ACC_FIXED || mode == ACC_PART) && nv <= kGroupMaxNodes && nt >= kGroupBlock / 2 && work >= 6.0e7 &&
-      ncells / ngroups >= 512)
+  if (((mode == ACC_FIXED && work >= 2.5e7) || (mode == ACC_PART && work >= 6.0e7)) && nv <= kGroupMaxNodes &&
+      nt >= kGroupBlock / 2 && ncells / ngroups >= 512)
     return kRecordsGroup;
-  return work >= 3.0e7 && ncells / ngroups >= 128 ? kRecordsDeal : kRecordsPlain;
+  return tile_fills_cu(mode, nv, ns) && work >= (faces ? 1.0e7 : 3.0e7) && ncells / ngroups >= 128 ? kRecordsDeal
+                                                                                                  : kRecordsPlain;
 }
 
 // Accumulation mode of the collide kernel (and the block size of the modes
@@ -817,7 +834,9 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   P.hyb_n = hn[1];
   P.hyb_ovf = hyb_rows ? reinterpret_cast<float*>(base + o_hyb) : nullptr;
   c->ngroups = ngroups;
-  c->records = seq ? kRecordsPlain : record_mode(cmode, ngroups, c->ncells, p->n_pairs, c->nv);
+  c->records = seq ? kRecordsPlain : record_mode(cmode, ngroups, c->ncells, p->n_pairs, c->nv, nsum, false);
+  c->face_records =
+      seq || p->order != 2 ? c->records : record_mode(cmode, ngroups, c->ncells, p->n_pairs, c->nv, nsum, true);
   P.grouped = c->records == kRecordsGroup ? 1 : 0;
   P.adj_win = (unsigned)std::min<int64_t>((int64_t)1 << 18, ((int64_t)1 << 30) / std::max<int64_t>(1, p->n_pairs));
   c->tidx = ngroups ? reinterpret_cast<uint2*>(base + o_tidx) : nullptr;
@@ -991,11 +1010,13 @@ static void launch_group(const boltz_ctx* c, uint2* tidx, float4* tcoef, hipStre
                      (int64_t)c->p.n_pairs, c->nv);
 }
 
-// The adjoint's two pair loops take their records dealt to lanes, not grouped
-// (64x64 cavity, 20^3, 20 000 pairs: reverse step 834 us dealt, 888 with a
-// grouped form of both loops, which spills).
-static int adjoint_records(const boltz_ctx* c) {
-  return c->records == kRecordsGroup ? kRecordsDeal : c->records;
+// The adjoint's two pair loops take their records dealt to lanes or in order, not
+// grouped (64x64 cavity, 20^3, 20 000 pairs: reverse step 834 us dealt, 888 with a
+// grouped form of both loops, which spills; 64x64, 16^3, 8000 records: collide
+// adjoint 317 us dealt, 313 in order).
+static int adjoint_records(const boltz_ctx* c, int records) {
+  if (records != kRecordsGroup) return records;
+  return tile_fills_cu(c->collide_mode, c->nv, c->n[0] + c->n[1] + c->n[2]) ? kRecordsDeal : kRecordsPlain;
 }
 
 // The face densities; with sample_step >= 0 (and samples_with_walls) the
@@ -1141,7 +1162,6 @@ static void launch_samples(boltz_ctx* c, uint32_t s32, hipStream_t st, const Rec
   }
 }
 
-
 // The collision with the records in R (drawn: already written this step).
 static int launch_collide_r(boltz_ctx* c, const float* hs, float* hout, int64_t step, uint32_t flags,
                             double* defect, hipStream_t st, bool drawn, const RecordTables& R) {
@@ -1209,7 +1229,7 @@ static int stream_step(boltz_ctx* c, const float* h_in, float* h_out, const bolt
   const bool cavity = c->p.bc == BOLTZ_BC_CAVITY;
   if (cavity && !walls_ok(walls, c->p.nx)) return fail(c, BOLTZ_EINVAL, "boltz_stream: cavity needs valid walls");
   int rc = BOLTZ_OK;
-  if (cavity) rc = launch_walls(c, h_in, make_walls(walls), walls, st, sample_step, c->records);
+  if (cavity) rc = launch_walls(c, h_in, make_walls(walls), walls, st, sample_step, c->face_records);
   if (drawn) *drawn = cavity && sample_step >= 0 && samples_with_walls(c);
   if (rc == BOLTZ_OK) rc = launch_stream(c, h_in, h_out, st);
   return rc;
@@ -1366,7 +1386,7 @@ static int launch_collide_adj(boltz_ctx* c, const float* hs, const double* lo, d
                               uint32_t flags, hipStream_t st, bool drawn = false) {
   const uint32_t s32 = (uint32_t)step;
   const bool table = c->ngroups > 0;
-  if (!drawn) launch_samples(c, s32, st, own_tables(c), adjoint_records(c));
+  if (!drawn) launch_samples(c, s32, st, own_tables(c), adjoint_records(c, c->records));
   const int block = c->adj_block[table ? 1 : 0];
   if (block == 256) launch_collide_adj_b<256>(c, table, hs, lo, ls, s32, flags, st);
   else if (block == 512) launch_collide_adj_b<512>(c, table, hs, lo, ls, s32, flags, st);
@@ -1428,7 +1448,7 @@ int boltz_step_adjoint(boltz_ctx* c, const float* h_in, const double* lam_out, d
   // forward streaming again (also leaves the face densities of h_in in P.nw),
   // the step's pair records drawn in its face launch as in boltz_step
   int rc = BOLTZ_OK;
-  if (cavity) rc = launch_walls(c, h_in, W, walls, st, step, adjoint_records(c));
+  if (cavity) rc = launch_walls(c, h_in, W, walls, st, step, adjoint_records(c, c->face_records));
   const bool drawn = cavity && step >= 0 && samples_with_walls(c);
   if (rc == BOLTZ_OK) rc = launch_stream(c, h_in, c->adj_hs, st);
   if (rc != BOLTZ_OK) return rc;

@@ -105,3 +105,31 @@ def test_collide_grouped_beyond_window(oracle_mod, kw):
         err = np.abs(got[cells[k]] - ref[k])
         assert (err <= 1e-5 * total).all(), (err / total).max()
     assert g.read_status() == 0
+
+
+@pytest.mark.parametrize("kw", [
+    dict(nx=24, ny=20, nv=(20, 20, 20), vmax=5.0, n_pairs=20833),     # below 1e7 record-cells: in order
+    dict(nx=24, ny=20, nv=(20, 20, 20), vmax=5.0, n_pairs=20834),     # dealt with the y faces, in order alone
+    dict(nx=64, ny=40, nv=(6, 6, 8), vmax=3.0, n_pairs=9765),         # small tile below 2.5e7: in order
+    dict(nx=64, ny=40, nv=(6, 6, 8), vmax=3.0, n_pairs=9766),         # grouped
+])
+def test_step_at_the_lines_of_the_record_rule(oracle_mod, kw):
+    import torch
+
+    import paper_1005_5405_amd as pkg
+
+    kw = dict(kw, delta=10.0, eps=0.1, mix16=4, sample_group=0)
+    print("[gpu-case] record rule", kw, flush=True)
+    g, o = pkg.Boltz(**kw), oracle_mod.Oracle(**kw)
+    w = pkg.Walls(lid_u=0.1)
+    h = torch.from_numpy(_state(g, 3)).cuda()
+    a, b, hs = g.empty(), g.empty(), g.empty()
+    g.step(h, a, w, 3)
+    g.stream(h, hs, w)
+    g.collide(hs, b, 3)
+    assert torch.equal(a, b)
+    cells = np.array([0, 7, g.ncells // 2, g.ncells - 1])
+    ref = o.collide_cells(hs.cpu().numpy().reshape(-1, g.nv)[cells].astype(np.float64), 3, cells)
+    err = np.abs(a.cpu().numpy().reshape(-1, g.nv)[cells] - ref).max(1)
+    assert (err <= 1e-5 * np.abs(ref).max(1)).all()
+    assert g.read_status() == 0
