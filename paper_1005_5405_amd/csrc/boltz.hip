@@ -301,22 +301,29 @@ int collide_block(int nv, int ns, bool sampler, bool continuous, int64_t n_pairs
   return 1024;
 }
 
-// Collide adjoint: false when its layout (with the sampler's tables) does
-// not fit next to 3360 bytes of reduction scratch.
+// Collide adjoint: false when its layout (with the sampler's tables) does not fit
+// next to 1440 bytes, the reduction scratch of its first form (the block sums now
+// use the accumulators' LDS; the limit stays, so the same grids are refused).
 bool adjoint_fits(int nv, int ns) { return collide_adj_lds(nv, ns, true, 64) + 1440 <= kLdsBytes; }
 
-// Threads per workgroup of the collide adjoint: its 128 registers a thread
-// allow 1024 threads per CU, so one workgroup of 1024 where the LDS or the
-// number of cells leaves a CU one cell, two of 512, else four of 256 (64x64
-// cavity, 20^3, shared pairs, one cell per CU by its LDS: 1024 threads 0.59
-// ms, 512 threads of the earlier form 0.71 ms).
-int adjoint_block(int nv, int ns, bool sampler, int64_t ncells, int ncu) {
+// Threads per workgroup of the collide adjoint (128 registers a thread: 1024
+// threads a CU; us a call):
+//   four of 256 where they fit and a CU gets four cells, with shared records two
+//   (32x16 cells, 12^3, 300 records: 21.2 against 24.1 with 512; 8^3, 2000 records
+//   22.4 against 26.1; own pairs 37.2 against 33.9);
+//   two of 512 where they fit, also for one cell a CU with shared records or few
+//   pairs of its own (16x16, 12^3: 2000 records 20.4 against 22.5 with 1024, 8000
+//   27.2 against 28.9; own pairs 300 16.3 against 18.4, 2000 24.8 against 25.1,
+//   8000 57.8 against 52.1);
+//   else one of 1024 (64x64 cavity, 20^3, shared records: 0.59 ms, 512 threads
+//   of the earlier form 0.71 ms).
+int adjoint_block(int nv, int ns, bool sampler, int64_t n_pairs, int64_t ncells, int ncu) {
   const int64_t cells = (ncells + ncu - 1) / ncu;
   auto fit = [&](int block) {
     return (int64_t)(kLdsBytes / (collide_adj_lds(nv, ns, sampler, block) + collide_adj_static_lds(block)));
   };
-  if (cells >= 4 && fit(256) >= 4) return 256;
-  if (cells >= 2 && fit(512) >= 2) return 512;
+  if (cells >= (sampler ? 4 : 2) && fit(256) >= 4) return 256;
+  if (fit(512) >= 2 && (cells >= 2 || !sampler || n_pairs < 2048)) return 512;
   return 1024;
 }
 
@@ -914,7 +921,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   }
   c->adj_supported = ea == hipSuccess && !seq && adjoint_fits(c->nv, nsum);
   for (int t = 0; t < 2 && ea == hipSuccess && c->adj_supported; ++t) {
-    const int block = adjoint_block(c->nv, nsum, t == 0, c->ncells, ncu < 1 ? 1 : ncu);
+    const int block = adjoint_block(c->nv, nsum, t == 0, p->n_pairs, c->ncells, ncu < 1 ? 1 : ncu);
     c->adj_block[t] = block;
     c->adj_lds[t] = collide_adj_lds(c->nv, nsum, t == 0, block);
     // (per kernel, shared by every context: the largest size)
