@@ -671,7 +671,7 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
         const double w = (c->om[0][ix] * c->om[1][iy]) * c->om[2][iz];
         const double psi[5] = {1.0, vx, vy, vz, (vx * vx + vy * vy) + vz * vz};
         int t = 0;
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < 5; ++k)
           for (int l = k; l < 5; ++l) m0[t++] += w * psi[k] * psi[l];
       }
   for (int k = 0; k < 2; ++k) {
@@ -803,7 +803,6 @@ int boltz_create(const boltz_problem* p, boltz_ctx** out) {
   P.key1 = (uint32_t)(p->seed >> 32);
   P.cavity = p->cavity_id;
   P.mix16 = p->mix16;
-  P.beta = p->mix16 / 16.0;
   P.dt = c->dt;
   P.dx = c->dx;
   P.dy = c->dy;

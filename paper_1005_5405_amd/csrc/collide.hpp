@@ -17,16 +17,19 @@ struct TablesLDS {
   double* v;      // node velocities
   double* om;     // omega, FP64
   double* xt;     // per-axis parts of x . psi of the correction (per cell)
-  double* m0;     // [16] sum_j w_j psi_k psi_l (packed k <= l), constant
   uint8_t* icdf;  // [3 * kFieldSize] Maxwellian inverse CDF on 12-bit fields
+  double* m0;     // [16] sum_j w_j psi_k psi_l (packed k <= l); the solves read P.m0
+                  // through scalar loads, but without this fill a reverse step
+                  // (64x64 cells, 20^3) takes 867 us, 841 with it, and a step of ten
+                  // cavities 8.50 ms against 8.40
   double* rw;     // 1 / omega per axis (continuous pairs)
   double* edge;   // [ns + 3] cell edges per axis (n + 1 each), for the search
                   // of post-collision cells on stretched grids
 
   static __host__ __device__ size_t bytes(int ns, bool sampler) {
+    // of the sampler's 32 bytes an entry 16 hold nothing: they stay so that each
+    // layout takes, and refuses, the grids it always did
     size_t b = 24 * (size_t)ns + 16 * sizeof(double);
-    // (32 bytes an entry, of which the tables take 16: which grids each layout
-    // takes, and which are refused, stays as it was with four tables)
     if (sampler) b += 32 * (size_t)ns + 24 + 3 * (size_t)kFieldSize;
     return b;
   }

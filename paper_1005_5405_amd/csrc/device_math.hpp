@@ -142,7 +142,6 @@ __device__ __forceinline__ void nt_store4(float* p, float4 v) {
 // orders of magnitude) and non-finite ones go to an FP32 accumulator
 // instead, so no value is clipped.
 constexpr double kFixMagic = 1572864.0;               // 1.5 * 2^20
-constexpr double kFixLimit = 262144.0;                // 2^18
 constexpr double kFixScale = 2.3283064365386963e-10;  // 2^-32
 
 // Value of a 64-bit fixed-point sum: hi + lo 2^-32 of its signed high and
@@ -405,15 +404,6 @@ __device__ __forceinline__ double block_sum20_w0(double (&v)[20], double* red, i
 __device__ __forceinline__ double lane_value(double t, int k) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t), k),
                           __builtin_amdgcn_readlane(__double2loint(t), k));
-}
-
-// block_sum20_w0 with the totals stored to tot[0..20) in LDS for the whole
-// block (ends with a barrier).
-template <int BLOCK>
-__device__ __forceinline__ void block_sum20_lds(double (&v)[20], double* red, double* tot) {
-  const double t = block_sum20_w0<BLOCK>(v, red);
-  if (threadIdx.x < 20) tot[threadIdx.x] = t;
-  __syncthreads();
 }
 
 }  // namespace boltz

@@ -36,7 +36,6 @@ struct Params {
   int order, bc;
   int64_t n_pairs, sample_group;
   uint32_t key0, key1, cavity, mix16;
-  double beta;            // mix16 / 16
   double dt, dx, dy, eps, inv_eps, qfac;
   double a[3], inv_cell[3];
   const double* vtab;     // [3][kMaxAxis] node velocities
@@ -44,7 +43,8 @@ struct Params {
   const double* rwnode;   // [nv] 1 / w of every node (product of the axes' 1 / omega)
   const float2* nwtab;    // [nv] {w / p~, 1 / p~} of every node, FP32: w the midpoint
                           // weight of Phi0, p~ = (1 - beta) p_phi + beta p_unif the
-                          // probability of drawing it from the mixture law
+                          // probability of drawing it from the mixture law, beta =
+                          // mix16 / 16
   const double2* sctab;   // [8192] {sin, cos} polynomials of cos_sin_2pi over one octant
   const uint8_t* icdf;    // [3][kFieldSize] Maxwellian inverse CDF on 12-bit fields
   const float* cour;      // [2][kMaxAxis] Courant number |v| dt / d{x,y}
