@@ -22,8 +22,10 @@ same workload calls boltz_stream and boltz_collide with HIP events recorded
 between them on the launch stream, to time each kernel group.
 
 Prints one JSON line: node-updates/s (value), pairs/s, the HBM roofline of the
-dominant kernel group, and the FP64 CPU oracle's throughput on a bounded
-sample of the same workload (a baseline only).
+dominant kernel group, rate and time of every variant, and the FP64 CPU oracle's
+throughput on a bounded sample of the same workload (a baseline only).  The whole
+record (kernels, rooflines, traces of every variant) is printed before it, after
+"[bench] record".
 """
 from __future__ import annotations
 
@@ -114,8 +116,40 @@ def alu_roofline(v):
             "note": "SQ_INSTS_VALU x 64 lanes over the HIP-event average of the launch"}
 
 
+def _round(x):
+    """Floats to six significant digits, through dicts and lists."""
+    if isinstance(x, float):
+        return float("%.6g" % x)
+    if isinstance(x, dict):
+        return {k: _round(v) for k, v in x.items()}
+    return [_round(v) for v in x] if isinstance(x, list) else x
+
+
+def short_line(d):
+    """The result line: every top-level field as it is, of each variant its
+    rate and time (the whole record is printed before it)."""
+    keep = ("value", "ms_per_step", "ms_per_adjoint_step", "wall_s", "finite")
+
+    def pick(v):
+        return {k: v[k] for k in keep if k in v}
+
+    out = {k: v for k, v in d.items() if k not in ("variants", "kernels", "kernel_timing", "pairs_per_s_meaning")}
+    out["variants"] = {}
+    for name, v in d.get("variants", {}).items():
+        if name == "full_length":
+            out["variants"][name] = {k: pick(w) for k, w in v.items()}
+        elif name == "batch":
+            out["variants"][name] = pick(v["graph"])
+        else:
+            out["variants"][name] = pick(v)
+    return _round(out)
+
+
 def _json_line(d):
-    print(json.dumps(d), flush=True)
+    # the whole record first (not a line of JSON), then the one result line,
+    # short enough for a log that keeps the last few thousand characters
+    print("[bench] record " + json.dumps(_round(d)), flush=True)
+    print(json.dumps(short_line(d)), flush=True)
 
 
 def _oracle_steps(oracle, preset, ny, threads, seconds_budget, max_steps=50):
