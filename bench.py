@@ -45,8 +45,11 @@ HBM_PEAK_GBS = 8000.0
 # and one FP32 write of h.  A whole step (stream + collide) moves 16 B/node.
 BYTES_PER_NODE_KERNEL = 8
 # LDS operations of one pair in one cell in the collision kernel: gathers of
-# h_a and h_b and four 64-bit integer atomic adds (Eq. monteCarloInt).
+# h_a and h_b and four 64-bit integer atomic adds (Eq. monteCarloInt); a shared
+# record in a quadruple of one first node takes a quarter of the gather and of
+# the loss there.
 LDS_READS_PER_PAIR, LDS_ATOMICS_PER_PAIR = 2, 4
+LDS_READS_GROUPED, LDS_ATOMICS_GROUPED = 1.25, 3.25
 N_CU, CLOCK_HZ = 256, 2.4e9
 # Random-address LDS rates on the MI355X, lane-operations per clock and CU,
 # measured by a standalone probe with every CU busy: ds_read_b32 (512 threads
@@ -489,6 +492,16 @@ def run_batch(pkg, torch, count: int, steps: int, warmup: int):
     return out
 
 
+def records_grouped(layout, ncells, n_pairs, nv, sample_group):
+    """Whether the library groups the shared records by their first node (the
+    lines of record_mode in boltz.hip)."""
+    line = {"fixed": 2.5e7, "part": 6.0e7}.get(layout)
+    if line is None or sample_group == 1:
+        return False
+    groups = 1 if sample_group == 0 else -(-ncells // sample_group)
+    return ncells * n_pairs >= line and nv <= 16384 and n_pairs >= 2048 and ncells // groups >= 512
+
+
 def _roofline(r, kw, g):
     """HBM roofline of the collision launch group (sample + collision
     kernels), 8 B/node per launch over its HIP-event average."""
@@ -496,35 +509,43 @@ def _roofline(r, kw, g):
     coll_gbs = BYTES_PER_NODE_KERNEL * nodes / t_c / 1e9
     pair_cells = g.ncells * g.n_pairs
     seq = bool(kw.get("flags", 0) & 8)
+    grouped = not seq and records_grouped(g.collide_layout, g.ncells, g.n_pairs, g.nv, kw["sample_group"])
     kernel = ("sample_kernel + seq_level_kernel + seq_collide_kernel" if seq
-              else "collide_kernel + sample_kernel + group_kernel" if kw["sample_group"] != 1 else "collide_kernel")
+              else "collide_kernel + sample_kernel + group_kernel" if grouped
+              else "collide_kernel + sample_kernel" if kw["sample_group"] != 1 else "collide_kernel")
     note = ("8 B/node (FP32 h read + write) per launch over the HIP-event average of the collision launch group; "
             "its in-place pair loop (4 LDS reads and 4 LDS writes per record, one level of the shared records "
             "at a time, latency-bound at one wavefront per cell), not HBM, sets its time" if seq else
             "8 B/node (FP32 h read + write) per launch over the HIP-event average of the collision "
-            "launch group; its pair loop (2 LDS gathers + 4 LDS integer atomic adds per pair and "
-            "cell), not HBM, sets its time")
+            "launch group; its pair loop (%g LDS gathers + %g LDS integer atomic adds per pair and "
+            "cell), not HBM, sets its time"
+            % ((LDS_READS_GROUPED, LDS_ATOMICS_GROUPED) if grouped else (LDS_READS_PER_PAIR, LDS_ATOMICS_PER_PAIR)))
     return {"kernel": kernel,
             "bound": "hbm", "achieved": coll_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": coll_gbs / HBM_PEAK_GBS, "traffic": measured_traffic(kw), "avg_ms": t_c * 1e3,
             "algorithmic_bytes_per_launch": BYTES_PER_NODE_KERNEL * nodes,
             "pair_cells_per_s_in_kernel": pair_cells / t_c,
             "lds_atomic_lane_ops_per_clk_per_cu": (None if seq else
-                                                   LDS_ATOMICS_PER_PAIR * pair_cells / t_c / (N_CU * CLOCK_HZ)),
+                                                   (LDS_ATOMICS_GROUPED if grouped else LDS_ATOMICS_PER_PAIR)
+                                                   * pair_cells / t_c / (N_CU * CLOCK_HZ)),
             # per-cell streams (G = 1) draw their pairs in the kernel: vector
             # issue, not the LDS, bounds that pair loop (the ALU roofline)
-            "lds_pair_loop": None if (seq or kw["sample_group"] == 1) else _lds_pair_bound(pair_cells, t_c),
+            "lds_pair_loop": None if (seq or kw["sample_group"] == 1) else _lds_pair_bound(pair_cells, t_c, grouped),
             "note": note}
 
 
-def _lds_pair_bound(pair_cells, t_c):
+def _lds_pair_bound(pair_cells, t_c, grouped=False):
     """Time the collision's pair loop needs at the probe's random-address LDS
-    rates (2 gathers + 4 64-bit adds per pair and cell), against the launch
-    group's measured average (which also holds the node phases, the tile
-    traffic and the sampler)."""
-    clk_per_pair = LDS_READS_PER_PAIR / LDS_READ_RATE + LDS_ATOMICS_PER_PAIR / LDS_ADD64_RATE
+    rates (2 gathers + 4 64-bit adds per pair and cell, 1.25 + 3.25 where every
+    record is in a quadruple of one first node), against the launch group's
+    measured average (which also holds the node phases, the tile traffic and the
+    sampler)."""
+    reads, adds = ((LDS_READS_GROUPED, LDS_ATOMICS_GROUPED) if grouped
+                   else (LDS_READS_PER_PAIR, LDS_ATOMICS_PER_PAIR))
+    clk_per_pair = reads / LDS_READ_RATE + adds / LDS_ADD64_RATE
     bound = pair_cells * clk_per_pair / (N_CU * CLOCK_HZ)
     return {"bound_ms": bound * 1e3, "frac": bound / t_c, "clk_per_pair_per_cu": clk_per_pair,
+            "gathers_per_pair": reads, "adds_per_pair": adds,
             "rates_lane_ops_per_clk_per_cu": {"ds_read_b32": LDS_READ_RATE, "ds_add_u64": LDS_ADD64_RATE},
             "note": "LDS-op time of the pair loop at the rates of a standalone random-address probe, "
                     "divided by the HIP-event average of the whole collision launch group"}

@@ -1,4 +1,4 @@
-"""bench.py's result line (no GPU needed)."""
+"""bench.py's result line and its LDS bound (no GPU needed)."""
 import json
 import sys
 
@@ -37,3 +37,13 @@ def test_result_line_is_short(capsys):
     assert set(got["variants"]["v0"]) == {"value", "ms_per_step"}
     assert json.loads(out[0][len("[bench] record "):])["variants"]["batch"]["tuned"]
 
+
+def test_lds_bound_counts_grouped_records():
+    bench = _bench()
+    a, b = bench._lds_pair_bound(1e8, 1e-3), bench._lds_pair_bound(1e8, 1e-3, True)
+    assert abs(b["bound_ms"] / a["bound_ms"] - (1.25 / 9.4 + 3.25 / 4.43) / (2 / 9.4 + 4 / 4.43)) < 1e-12
+    assert bench.records_grouped("fixed", 4096, 20000, 8000, 0)
+    assert not bench.records_grouped("fixed", 1024, 20000, 8000, 0)
+    assert bench.records_grouped("part", 40000, 50000, 13824, 0)
+    assert not bench.records_grouped("fixed", 4096, 20000, 8000, 64)
+    assert not bench.records_grouped("hybrid", 40000, 50000, 13824, 0)
