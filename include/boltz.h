@@ -262,8 +262,8 @@ int boltz_step(boltz_ctx* ctx, const float* h_in, float* h_out, const boltz_wall
 /* Adjoint of boltz_stream (Sec. 3, Eq. streaming2D / the Beam-Warming
  * sweeps, with the wall emission of Eq. bcMax): lam_in = (dh_out/dh_in)^T
  * lam_out, where h_out = boltz_stream(h_in).  h_in: the FP32 state that was
- * streamed.  lam_in must not overlap lam_out.  Order 2 needs the
- * BOLTZ_WITH_ADJOINT scratch. */
+ * streamed.  lam_in must not overlap lam_out.  Order 2 needs a context
+ * created with BOLTZ_WITH_ADJOINT (EINVAL otherwise). */
 int boltz_stream_adjoint(boltz_ctx* ctx, const float* h_in, const double* lam_out, double* lam_in,
                          double* grad_walls, const boltz_walls* walls, void* stream);
 
@@ -295,7 +295,10 @@ int boltz_lid_shear_adjoint(boltz_ctx* ctx, const float* h, const boltz_walls* w
  * the streaming of every problem, the shared-sample records of every
  * problem, and one persistent collision launch over a work list of
  * (problem, cell) items sorted by decreasing cost.  Every problem's result
- * is bitwise that of boltz_step on the problem alone.  The step number is a
+ * is that of boltz_step on the problem alone: bit for bit in the fixed-point
+ * layouts where both collide with the same threads per workgroup
+ * (boltz_info.collide_block, boltz_batch_set_class), else up to the rounding
+ * of FP64 moment sums added in another order.  The step number is a
  * device counter (boltz_batch_set_step; boltz_batch_step advances it), so a
  * captured HIP graph of boltz_batch_step calls replays successive steps.
  * All problems must share the streaming order and have nv[2] % 4 == 0. */
