@@ -379,6 +379,19 @@ __device__ __forceinline__ double wave_fold5(double (&v)[5], int lane) {
   return t;
 }
 
+// Sum of 8 values per lane over the wavefront: lane 32 b5 + 16 b4 + 8 b3
+// holds value k = 4 b5 + 2 b4 + b3.
+__device__ __forceinline__ double wave_fold8(double (&v)[8], int lane) {
+  fold_half<8, 32, 0>(v, lane);
+  fold_half<4, 16, 0>(v, lane);
+  fold_half<2, 8, kDppMirror>(v, lane);
+  double t = v[0];
+  t += dpp_f64<kDppHalfMirror>(t);
+  t += dpp_f64<kDppXor2>(t);
+  t += dpp_f64<kDppXor1>(t);
+  return t;
+}
+
 template <int BLOCK>
 __device__ __forceinline__ double block_sum20_w0(double (&v)[20], double* red, int nwd = BLOCK / 64) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = BLOCK / 64;

@@ -224,14 +224,17 @@ __device__ __forceinline__ float xswept_value(const Params& P, const float* h, i
 // that a wall at rest (R = 1) gives D = A bitwise.  Launched only when the
 // wall state changes.  One workgroup a wall is bound by latency: a thread
 // forms an outgoing node and its mirror image together, so nothing is read
-// back from the table behind a barrier (200x200 cells, 24^3, moving lid: 6 us
-// less a step; a 64x64, 20^3 context's first step 409 -> 402 us).
+// back from the table behind a barrier; the sums are folded by lane swaps,
+// and the derivatives' divisions are left to the totals (a launch for the lid
+// alone: 8^3 3.5 us, 12^3 6.1, 20^3 13.0, 24^3 19.2; 10.2, 12.3, 18.2 and 24.4 with
+// eight shuffled sums and the derivatives divided node by node).
 constexpr int kWallConstBlock = 1024;
 
 // Blocks first, first + 1, ... of the full set (0 left, 1 right, 2 top, 3 +
 // i bottom face i): a change of the lid alone rebuilds block 2 only.
 __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, WallArgs W, int first) {
-  __shared__ double red[8 * (kWallConstBlock / 64)];
+  constexpr int NW = kWallConstBlock / 64;
+  __shared__ double red[8 * NW];
   const int b = (int)blockIdx.x + first;
   const int wall = b == 0 ? WALL_LEFT : (b == 1 ? WALL_RIGHT : (b == 2 ? WALL_TOP : WALL_BOTTOM));
   const int pos = b < 3 ? 0 : b - 3;
@@ -263,27 +266,47 @@ __global__ __launch_bounds__(kWallConstBlock) void wallconst_kernel(Params P, Wa
     s[1] += aw * Rm;
     if (wall == WALL_TOP) {
       // the lid's part of the shear on it and of its derivatives (incoming
-      // nodes, v_y < 0), which depend on the walls alone
+      // nodes, v_y < 0), which depend on the walls alone: w v_x v_y and |v_y| w
+      // times 1, R, and the factors u = v_x - U and |v - U|^2 of R in dR
       const double w = (P.omtab[mx] * P.omtab[kMaxAxis + my]) * P.omtab[2 * kMaxAxis + jz];
-      double dU, dT;
-      wall_ratio_grad(Rm, m1, m2, v3, Uw, tau, dU, dT);
-      const double c = w * m1 * m2, awm = fabs(m2) * w;
+      const double ux = m1 - Uw, c2 = (ux * ux + m2 * m2) + v3 * v3;
+      const double c = w * m1 * m2, cR = c * Rm, aR = (fabs(m2) * w) * Rm;
       s[2] += c;
-      s[3] += c * Rm;
-      s[4] += c * dU;
-      s[5] += c * dT;
-      s[6] += awm * dU;
-      s[7] += awm * dT;
+      s[3] += cR;
+      s[4] += cR * ux;
+      s[5] += cR * c2;
+      s[6] += aR * ux;
+      s[7] += aR * c2;
     }
   }
-  if (wall == WALL_TOP) block_sum<8>(s, red);
-  else block_sum<2>(reinterpret_cast<double(&)[2]>(s), red);
-  if (threadIdx.x == 0) {
+  const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
+  const double t = wave_fold8(s, lane);
+  if ((lane & 7) == 0) red[(lane >> 3) * NW + wid] = t;
+  __syncthreads();
+  if (wid > 0) return;
+  // lane k < 8: total k
+  double v = 0.0;
+  if (lane < 8) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) v += red[lane * NW + w];
+  }
+  const double D = lane_value(v, 1), it = 1.0 / tau;
+  if (lane == 0) {
     double* k = const_cast<double*>(wall_consts(P, wall, pos));
-    k[0] = s[0];
-    k[1] = s[1];
-    if (wall == WALL_TOP)
-      for (int i = 0; i < 6; ++i) P.wlid[i] = s[2 + i];
+    k[0] = v;
+    k[1] = D;
+  }
+  if (wall != WALL_TOP) return;
+  // dR/dU = 2 u R / tau, dR/dtau = (|v - U|^2 / tau - 3/2) R / tau
+  const double s2 = lane_value(v, 2), s3 = lane_value(v, 3), s4 = lane_value(v, 4), s5 = lane_value(v, 5),
+               s6 = lane_value(v, 6), s7 = lane_value(v, 7);
+  if (lane == 0) {
+    P.wlid[0] = s2;
+    P.wlid[1] = s3;
+    P.wlid[2] = (2.0 * s4) * it;
+    P.wlid[3] = (s5 * it - 1.5 * s3) * it;
+    P.wlid[4] = (2.0 * s6) * it;
+    P.wlid[5] = (s7 * it - 1.5 * D) * it;
   }
 }
 
