@@ -275,27 +275,29 @@ bool pick_collide(int nv, int ns, int& mode, int (&blocks)[2]) {
 // CU: the most that one gets; 128 registers a thread at 1024 and 512 threads,
 // up to 168 at 256):
 //   one workgroup of 1024 where the LDS or the number of cells gives a CU one
-//   cell at a time (64x64, 20^3: 280 against 311 with 512; 16x16, 12^3, 3000
-//   own pairs 16.0 against 23.2 with 256);
+//   cell at a time (64x64, 20^3: 261 against 348 with 512; 16x16, 12^3, 3000 own
+//   pairs 16.0 against 23.2 with 256);
 //   three of 256 where they fit and a CU gets three cells (33x21, 13x11x9, 3001
-//   shared records: 20.5 against 24.8 with 512), with shared records two (576
+//   shared records: 34.4 against 38.4 with 512), with shared records two (576
 //   cells, 14^3, 8000: 31.4 against 33.5; 8^3, 300: 12.8 against 15.1);
-//   two of 512 between (32x24, 16^3, 8000 records: 34 against 41 with 1024; 576
-//   cells, 16^3, 8000: 36.4 against 37.7 with two of 256).
+//   two of 512 between (32x24, 16^3, 8000 records: 36.5 against 37.6 with two of
+//   256 and 43.2 with 1024).
 // A light pair loop does not fill more than 256 threads: fewer than two records a
 // thread (16x16 cells, 8^3, 300 records: 12.1 against 13.0 with 1024, even at
-// 1000), with drawn pairs fewer than three draws a thread where a CU has two
-// cells (32x32, 8^3, 300 continuous pairs 28.6 against 31.4 with 512, 1000
-// pairs 49.0 against 52.1, 64x64 82.7 against 101 and 188 against 183).
+// 1000), with drawn pairs fewer than three draws a thread, continuous ones four,
+// where a CU has two cells (32x16, 8^3, 300 own pairs 11.9 against 13.0 with 512,
+// 1000 15.7 against 15.5; continuous pairs, 32x32, 300 27.1 against 28.9, 1000
+// 42.2 against 47.7, 64x64, 300 76.1 against 92.9, 1000 165.1 against 166.3).
 // Continuous pairs beyond that need every wavefront the registers allow: two
-// of 512 (25x67, 8x21x7, 6246 own pairs: 364 a step against 456 with three of
-// 256; 64x64, 12^3, 3000: 460 against 507).
+// of 512 (25x67, 8x21x7, 6246 own pairs: 378 a step against 402 with three of
+// 256; 64x64, 12^3, 3000: 414 a collision against 440).
 int collide_block(int nv, int ns, bool sampler, bool continuous, int64_t n_pairs, int64_t ncells, int ncu) {
   const int64_t cells = (ncells + ncu - 1) / ncu;
   auto fit = [&](int block) {
     return (int64_t)(kLdsBytes / (CollideLDS::bytes(nv, ns, ACC_FIXED, sampler) + collide_static_lds(block)));
   };
-  if (sampler ? n_pairs < 768 && cells >= 2 && fit(256) >= 2 : n_pairs < 512 && fit(256) >= 2) return 256;
+  const bool light = n_pairs < (!sampler ? 512 : continuous ? 1024 : 768);
+  if (light && (cells >= 2 || !sampler) && fit(256) >= 2) return 256;
   if (cells >= (sampler ? 3 : 2) && fit(256) >= 3 && !(sampler && continuous)) return 256;
   if (cells >= 2 && fit(512) >= 2) return 512;
   return 1024;

@@ -873,8 +873,9 @@ namespace boltz {
 // row of cells over v_y > 0 (w v_x v_y h, and w v_y h for the
 // lid's density n_w = (A + eps B) / D); the re-emitted part is n_w times a sum
 // that depends on the walls alone (wlid).  The last workgroup of the top row
-// adds the faces.  64x64 cells, 20^3: 35 us with the lid (3.8 TB/s), 41 + 5 with rows
-// read in place, a node loop per lid face and a launch to add the faces.
+// adds the faces.  64x64 cells, 20^3: 37.7 us a call with the lid (3.5 TB/s), 49.5 with
+// rows read in place, a node loop per lid face and a launch to add the faces; 46.0
+// and 57.5 where the walls change with every call (the table's launch before it).
 constexpr int kMomentsBlock = 512;
 constexpr int kMomentsStage = 15872;  // largest cell staged: 62 KB, under 64 KB with the block sums
 
