@@ -143,7 +143,9 @@ __device__ __forceinline__ void wall_ratio_grad(double R, double vx, double vy, 
 }
 
 // A value for the last workgroup of this launch (below): written at the
-// device's point of coherence, complete before the function returns.
+// device's point of coherence, complete before the function returns.  The
+// order of the two atomics is that of gfx950 (the wait ends when the device-wide
+// exchange has been done), more than the language promises for relaxed ones.
 __device__ __forceinline__ void publish(double* p, double v) {
   (void)__hip_atomic_exchange(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v),
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
