@@ -67,16 +67,16 @@ PAPER_NODE_UPDATES_PER_S = 1.0e9
 # summaries under profiles/, step_kernels_grouped.md for the current ones).
 TRAFFIC = {
     # sample_kernel + group_kernel + collide_kernel<1024, true, ACC_PART>
-    "200x200_24_G0": {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "fetch_kib": 1476.1 + 618.4 + 1088089.9, "fetch_scale": 1.99993,
-                      "write_kib": 1171.88 + 1171.88 + 2169216.5, "write_scale": 1.0},
+    "200x200_24_G0": {"sha256": "689e42d459ffe504f1c9d083b6d4a0707bd5932f85e285694532461bc760af26", "fetch_kib": 1476.8 + 622.9 + 1087851.5, "fetch_scale": 1.99994,
+                      "write_kib": 1171.88 + 1171.88 + 2169216.0, "write_scale": 1.0},
     # sample_kernel + group_kernel + collide_kernel<1024, true, ACC_FIXED>
-    "64x64_20_G0": {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "fetch_kib": 1050.6 + 254.7 + 66090.0, "fetch_scale": 1.99943,
+    "64x64_20_G0": {"sha256": "689e42d459ffe504f1c9d083b6d4a0707bd5932f85e285694532461bc760af26", "fetch_kib": 1050.6 + 257.5 + 66090.0, "fetch_scale": 1.99942,
                     "write_kib": 468.75 + 468.75 + 128000.0, "write_scale": 1.0},
 }
 # VALU instructions (wave64) per dispatch of the per-cell-sample (G = 1)
 # collision kernel of the 64x64 cavity, rocprofv3 --pmc SQ_INSTS_VALU; valid
 # for the recorded kernel-source SHA-256.
-VALU_G1 = {"sha256": "c66389caa340adfe8f3c2a914a417e8f0cdd91360eb6e41adc95f20071812769", "valu_insts_per_dispatch": 3.43980e8}
+VALU_G1 = {"sha256": "689e42d459ffe504f1c9d083b6d4a0707bd5932f85e285694532461bc760af26", "valu_insts_per_dispatch": 3.43976e8}
 KERNEL_SOURCES = ("adjoint.hpp", "boltz.hip", "collide.hpp", "device_math.hpp", "kernels.hpp", "sequential.hpp")
 
 
